@@ -65,7 +65,7 @@ constexpr int kSub = 32;   // tokens per tile
 constexpr int kNBuf = 4;   // LDS tile buffers per workgroup
 constexpr int kDepth = 3;  // tiles in flight while one is consumed
 constexpr int kWgsPerCu = 2;
-constexpr int kPrefillWaves = 4;  // waves per prefill workgroup (4 or 8)
+constexpr int kPrefillWaves = 4;  // waves per prefill workgroup (32 query rows each)
 
 template <int D>
 struct Smem {
@@ -1071,15 +1071,31 @@ __global__ __launch_bounds__(kThreads) void kv_append_dev_kernel(
 //
 // Causal attention of tokens just appended to a node, over its chain (a
 // query's shared prompt, prefilled once for all of its rollouts).  A
-// workgroup takes up to 128 consecutive new tokens of one sequence for one
-// query head; with W waves (4 or 8), wave w owns tokens [R w, R w + R),
-// R = 128 / W, as R / 16 row blocks that share every K and V operand it reads
-// from LDS.  Eight waves of 16 rows keep the registers under 128 per lane,
-// so that four waves share each SIMD and hide each other's latencies.  The workgroup streams the
-// 32-token tiles of the chain up to its last token through the decode's
-// four-buffer global->LDS pipeline.  Tiles that every row of a wave sees in
-// full take the unmasked path; the others mask keys past each row's own
-// position and, at a node's end, past the tile's tokens.
+// workgroup of four waves takes up to 128 consecutive new tokens of one
+// sequence for one query head; wave w owns rows [32 w, 32 w + 32).  The
+// workgroup streams the 32-token tiles of the chain up to its last token
+// through LDS.
+//   QK: S^T = K Q^T with v_mfma_f32_32x32x16_bf16 (A = 32 K rows, B = Q^T),
+//       the K rows read in the order pf_tau, so that the lane's 16 scores are
+//       tokens 16 s + 8 (lane / 32) + 0..7 (s = 0, 1) of its query row lane %
+//       32 -- the B operand of the PV product, so P never leaves registers.
+//   PV: O^T += V^T P^T, 32 d-rows of V^T by 16 tokens per instruction, P as
+//       hi + lo bf16 terms (softmax weights to about 16 bits).
+// A step holds K of tile k + 1 and V of tile k: the QK of the next tile, this
+// tile's weights and its PV are one block of straight code, so the vector
+// work issues between the matrix instructions.  Tile k's partial tokens and
+// the causal limit are applied to the scores (rare, wave-uniform branch), and
+// V entries past a partial tile's tokens are cleared in LDS.
+//
+// Bound: the matrix cores at the clock that their power leaves.  At 8 prompts
+// of 2048 tokens (Hq 40, Hkv 8, D 128) the kernel executes 1.13 PFLOP/s of
+// matrix work (two thirds of it algorithmic: the lo terms), at about 2.0 GHz;
+// an 8192^3 library product reaches 1.20 on the same card.  Against the form
+// with 16x16x32 products, a branch per stage, non-temporal tile loads and
+// 16-byte stores: 602 -> 476 us there, 546 -> 430 us for 64 prompts of
+// 256-1024 tokens (Hq 28, Hkv 4), 25.6 -> 20 us for one of 513.  Of that:
+// the larger product in straight code 10%, cached tile loads 6% (the G heads
+// and the items of a sequence share them), whole-row stores 5%.
 //
 // Work order: a unit is (item, KV head); the host lists each XCD's units,
 // longest first, keeping a sequence's units for one KV head on one XCD where
@@ -1087,80 +1103,59 @@ __global__ __launch_bounds__(kThreads) void kv_append_dev_kernel(
 // on that XCD gives slot s / G of the schedule and head h = g G + s % G, so
 // the G query heads of a unit run on one XCD at about the same time and the
 // chain's K/V tiles are reused through that XCD's L2.
-// The prefill's tile loads: a 32-token tile is 2 D / 16 slots of 1 KiB (K
-// rows, then V^T rows, swizzled as for the decode); each of the W waves
-// issues D / (8 W) of them per tile, one 16-byte global->LDS load per lane
-// each, so every wave counts the same number of loads per tile.
-template <int D, int W>
-struct PfPipe {
-  static constexpr int kKSlots = kSub * D * 2 / 1024;
-  static constexpr int kSlots = 2 * kKSlots / W;  // per wave
-  uint32_t buf0;
-  uint32_t off[kSlots];
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-  __device__ __forceinline__ void init(uint32_t b0, int wave, int lane) {
-    constexpr int kKChunks = D / 8;
-    buf0 = b0;
-#pragma unroll
-    for (int j = 0; j < kSlots; ++j) {
-      const int sl = wave * kSlots + j;
-      if (sl < kKSlots) {
-        const int c = sl * 64 + lane;
-        const int row = c / kKChunks;
-        off[j] = row * (D * 2) + (((c % kKChunks) ^ k_swz(row)) << 4);
-      } else {
-        const int c = (sl - kKSlots) * 64 + lane;
-        const int vrow = c >> 2;
-        off[j] = v_chunk_off<D>(vrow, (c & 3) ^ v_swz(vrow));
-      }
-    }
-  }
-  // Stages the tile whose first row is pool row 16 t16 into the buffer at
-  // LDS byte address dst.
-  __device__ __forceinline__ void issue(const uint16_t* __restrict__ kpool, const uint16_t* __restrict__ vpool,
-                                        int t16, uint32_t dst, int wave) const {
-    const int64_t o = static_cast<int64_t>(t16) * kVGroup * D;
-#pragma unroll
-    for (int j = 0; j < kSlots; ++j) {
-      const int sl = wave * kSlots + j;
-      if (sl < kKSlots)
-        dma16s(kpool + o, off[j], __builtin_amdgcn_readfirstlane(dst + sl * 1024));
-      else
-        dma16s(vpool + o, off[j], __builtin_amdgcn_readfirstlane(dst + kSub * D * 2 + (sl - kKSlots) * 1024));
-    }
-  }
-  // Waits for tile k when up to `cap` newer tiles may have been issued, and
-  // publishes it.
-  __device__ __forceinline__ void wait(int k, int ntot, int cap) const {
-    const int ahead = ntot - 1 - k < cap ? ntot - 1 - k : cap;
-    if (ahead >= 2)
-      barrier_tile_landed<2 * kSlots>();
-    else if (ahead == 1)
-      barrier_tile_landed<kSlots>();
-    else
-      barrier_tile_landed<0>();
-  }
-};
+__device__ __forceinline__ f32x16 mfma32(const uint4& a, const uint4& b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c,
+                                                 0, 0, 0);
+}
+
+// Token (K row of the tile) of row m of the QK operand: output row
+// m = 8 q + 4 h + e is register 4 q + e of lane half h.
+__device__ __forceinline__ int pf_tau(int m) {
+  return 16 * (m >> 4) + 8 * ((m >> 2) & 1) + 4 * ((m >> 3) & 1) + (m & 3);
+}
+
+// As dma16s, but cached (a sequence's tiles are read by every query head of
+// the group and by all of its items) and free to move among the LDS reads and
+// arithmetic between two barriers.
+__device__ __forceinline__ void dma16c(const void* sbase, uint32_t voff, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+               :: "v"(voff), "s"(sbase), "s"(lds) : "m0");
+}
+
+// Groups of tile loads in flight while a tile is computed: one covers the L2
+// latency (three measured the same, and need twice the LDS).
+constexpr int kPfAhead = 1;
+constexpr int kPfStages = kPfAhead + 1;  // LDS buffers of each of K and V
 
 template <int D, int W>
-__global__ __launch_bounds__(64 * W, W / 2) void prefill_kernel(
+__global__ __launch_bounds__(64 * W, 2) void prefill_kernel(
     const uint16_t* __restrict__ kpool, const uint16_t* __restrict__ vpool, const uint16_t* __restrict__ q,
     const PrefillItem* __restrict__ items, const int2* __restrict__ tiles, const int32_t* __restrict__ sched,
     float* __restrict__ out, float* __restrict__ lse, int32_t n_sched, int32_t rows16, int32_t hq, int32_t hkv,
     float scale_log2) {
-  constexpr int kKS = D / 32;  // QK k-steps
-  constexpr int kDB = D / 16;  // PV output d-blocks
-  constexpr int kRB = 8 / W;   // 16-row blocks per wave
-  constexpr int kRows = 16 * kRB;
-  constexpr uint32_t kBufBytes = 2 * kSub * D * 2;
-  __shared__ __attribute__((aligned(16))) uint16_t kv[kNBuf][2 * kSub * D];
+  constexpr int kKS = D / 16;                       // QK k-steps
+  constexpr int kDB = D / 32;                       // PV output d-blocks
+  constexpr int kHalf = kSub * D * 2;               // bytes of a K (or V^T) tile
+  constexpr int kPer = kHalf / 1024 / W;            // 1 KiB slots per wave for each of K and V
+  constexpr int kKChunks = D / 8;
+  constexpr int kQBytes = 32 * D * 2;               // a wave's query rows
+  // K stages, V stages, every wave's query rows; at the end, its output rows
+  __shared__ __attribute__((aligned(1024))) char smem[2 * kPfStages * kHalf + W * kQBytes];
+  static_assert(sizeof(smem) >= W * 2 * kQBytes, "output rows fit");
+  char* const kbuf = smem;
+  char* const vbuf = smem + kPfStages * kHalf;
+  char* const qbuf = smem + 2 * kPfStages * kHalf;
 
   const int G = hq / hkv;
   const int wg = blockIdx.x;
   const int s_x = wg >> 3;
   const int slot = (s_x / G) * 8 + (wg & 7);
   if (slot >= n_sched) return;  // whole workgroup
-  const int unit = sched[slot];
+  int zero = 0;
+  asm volatile("" : "+v"(zero));  // a vector load, beside the scalar loads of the arguments
+  const int unit = __builtin_amdgcn_readfirstlane(sched[slot + zero]);
   if (unit < 0) return;
   const int item_i = unit / hkv;
   const int g = unit - item_i * hkv;
@@ -1168,195 +1163,241 @@ __global__ __launch_bounds__(64 * W, W / 2) void prefill_kernel(
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int a = lane >> 4;    // lane group
-  const int r16 = lane & 15;  // row within a 16-row block
+  const int half = lane >> 5;
+  const int r32 = lane & 31;
   const PrefillItem it = items[item_i];
   const int nk = it.nk;
   const int2* __restrict__ tl = tiles + it.tile_off;
   const int hb_base = g * rows16;  // KV head g's pool rows start at row 16 hb_base
 
-  // Q^T operands: lane holds row kRows wave + 16 rb + r16, d chunk 4 ks + a
-  uint4 qb[kRB][kKS];
+  // The wave's query rows into its share of the LDS (rows past the item's
+  // last repeat it), chunk c of row r at c ^ (r & 15) (r & 7 at D = 64).
+  {
+    constexpr int kQCh = D / 8;
+    const uint16_t* qp = q + (static_cast<int64_t>(it.row0) * hq + h) * D;
 #pragma unroll
-  for (int rb = 0; rb < kRB; ++rb) {
-    const int m = kRows * wave + 16 * rb + r16;
-    if (m < it.n_rows) {
-      const uint4* src = reinterpret_cast<const uint4*>(q + (static_cast<int64_t>(it.row0 + m) * hq + h) * D);
-#pragma unroll
-      for (int ks = 0; ks < kKS; ++ks) qb[rb][ks] = src[4 * ks + a];
-    } else {
-#pragma unroll
-      for (int ks = 0; ks < kKS; ++ks) qb[rb][ks] = make_uint4(0, 0, 0, 0);
+    for (int j = 0; j < kQBytes / 1024; ++j) {
+      const int c = j * 64 + lane;
+      const int r = c / kQCh;
+      const int row = 32 * wave + r < it.n_rows ? 32 * wave + r : it.n_rows - 1;
+      dma16(qp + static_cast<int64_t>(row) * hq * D + ((c % kQCh) ^ (r & (kQCh - 1))) * 8,
+            __builtin_amdgcn_readfirstlane(lds_addr(qbuf) + wave * kQBytes + j * 1024));
     }
   }
-  // The query loads land before the first tile is issued: otherwise the
-  // compiler, which does not see the tile loads, would wait for them (and so
-  // drain the tile pipeline) at their first use inside the loop.
-#pragma unroll
-  for (int rb = 0; rb < kRB; ++rb)
-#pragma unroll
-    for (int ks = 0; ks < kKS; ++ks) asm volatile("" ::"v"(qb[rb][ks].x));
 
-  PfPipe<D, W> pp;
-  pp.init(lds_addr(kv[0]), wave, lane);
-  for (int k = 0; k < kDepth && k < nk; ++k) pp.issue(kpool, vpool, hb_base + tl[k].x, pp.buf0 + k * kBufBytes, wave);
-  int2 next = kDepth < nk ? tl[kDepth] : make_int2(0, 0);
-
-  const int row_w = kRows * wave;  // the wave's first row
-  const bool wave_on = row_w < it.n_rows;
-  const int pos_lo = it.pos0 + row_w;
-  const int pos_hi = it.pos0 + (row_w + kRows - 1 < it.n_rows - 1 ? row_w + kRows - 1 : it.n_rows - 1);
-  int prow[kRB];
+  // This lane's byte offsets in a tile's K and V^T ranges (swizzles applied
+  // on the global side, as for the decode).
+  uint32_t koff[kPer], voff[kPer];
 #pragma unroll
-  for (int rb = 0; rb < kRB; ++rb) prow[rb] = it.pos0 + row_w + 16 * rb + r16;
-
-  f32x4 acc[kRB][kDB];
-#pragma unroll
-  for (int rb = 0; rb < kRB; ++rb)
-#pragma unroll
-    for (int db = 0; db < kDB; ++db) acc[rb][db] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m_ref[kRB], l_sum[kRB];
-#pragma unroll
-  for (int rb = 0; rb < kRB; ++rb) {
-    m_ref[rb] = -INFINITY;
-    l_sum[rb] = 0.f;
+  for (int j = 0; j < kPer; ++j) {
+    const int c = (wave * kPer + j) * 64 + lane;
+    const int row = c / kKChunks;
+    koff[j] = row * (D * 2) + (((c % kKChunks) ^ k_swz(row)) << 4);
+    const int vrow = c >> 2;
+    voff[j] = v_chunk_off<D>(vrow, (c & 3) ^ v_swz(vrow));
   }
-
-  // S^T = K Q^T for the 32 tokens of tile k, both row blocks
-  auto qk = [&](int k, f32x4 (&S)[kRB][2]) {
-    const char* kt = reinterpret_cast<const char*>(kv[k & (kNBuf - 1)]);
+  const uint32_t kb = lds_addr(kbuf) + wave * kPer * 1024, vb = lds_addr(vbuf) + wave * kPer * 1024;
+  // (`on` 0: a load that keeps its place in the load count, every lane reading
+  // the tile's first 16 bytes)
+  auto issue_k = [&](int t16, int st, uint32_t on) {
+    const uint16_t* p = kpool + static_cast<int64_t>(hb_base + t16) * kVGroup * D;
 #pragma unroll
-    for (int rb = 0; rb < kRB; ++rb) S[rb][0] = S[rb][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < kPer; ++j) dma16c(p, koff[j] & on, __builtin_amdgcn_readfirstlane(kb + st * kHalf + j * 1024));
+  };
+  auto issue_v = [&](int t16, int st, uint32_t on) {
+    const uint16_t* p = vpool + static_cast<int64_t>(hb_base + t16) * kVGroup * D;
 #pragma unroll
-    for (int ks = 0; ks < kKS; ++ks) {
-#pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        const int tok = tau(b, r16);
-        const int c = 4 * ks + a;
-        const uint4 ka = *reinterpret_cast<const uint4*>(kt + tok * (D * 2) + ((c ^ k_swz(tok)) << 4));
-#pragma unroll
-        for (int rb = 0; rb < kRB; ++rb) S[rb][b] = mfma16(ka, qb[rb][ks], S[rb][b]);
-      }
-    }
+    for (int j = 0; j < kPer; ++j) dma16c(p, voff[j] & on, __builtin_amdgcn_readfirstlane(vb + st * kHalf + j * 1024));
   };
 
-  // weights of tile k (lazy reference per row, as in the decode), then
-  // O^T += V^T P^T with one V operand per d-block for both row blocks
-  auto softmax_pv = [&](int k, const f32x4 (&S)[kRB][2], int first, int cnt) {
-    const char* vt = reinterpret_cast<const char*>(kv[k & (kNBuf - 1)]) + kSub * D * 2;
-    const bool full = cnt == kSub && first + kSub - 1 <= pos_lo;
-    uint4 P[kRB], PL[kRB];
+  const int row_w = 32 * wave;  // the wave's first row
+  const bool wave_on = row_w < it.n_rows;
+  const int pos_lo = it.pos0 + row_w;
+  const int pos_hi = it.pos0 + (row_w + 31 < it.n_rows - 1 ? row_w + 31 : it.n_rows - 1);
+  const int prow = pos_lo + r32;
+
+  // records of tiles k .. k + kPfAhead + 1
+  int2 rec[kPfAhead + 2];
 #pragma unroll
-    for (int rb = 0; rb < kRB; ++rb) {
-      float x[2][4];
-      float mx = -INFINITY;
-      if (full) {
-        // every key visible: max over the raw scores (the scale is positive)
-        mx = fmaxf(fmaxf(fmaxf(S[rb][0][0], S[rb][0][1]), fmaxf(S[rb][0][2], S[rb][0][3])),
-                   fmaxf(fmaxf(S[rb][1][0], S[rb][1][1]), fmaxf(S[rb][1][2], S[rb][1][3]))) * scale_log2;
-      } else {
+  for (int t = 0; t < kPfAhead + 2; ++t) rec[t] = tl[t < nk ? t : nk - 1];
+  // Loads in order: K of tile 0, then groups t = {V of tile t, K of tile
+  // t + 1}, kPfAhead groups ahead, each as many loads whatever t is.
+  issue_k(rec[0].x, 0, ~0u);
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+  for (int t = 0; t < kPfAhead; ++t) {
+    issue_v(rec[t].x, t, t < nk ? ~0u : 0u);
+    issue_k(rec[t + 1].x, t + 1, t + 1 < nk ? ~0u : 0u);
+  }
+
+  uint4 qb[kKS];
+  f32x16 acc[kDB];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int t = 8 * a + 4 * b + e;
-            x[b][e] = t < cnt && first + t <= prow[rb] ? S[rb][b][e] * scale_log2 : -INFINITY;
-            mx = fmaxf(mx, x[b][e]);
-          }
-      }
-      if (__builtin_amdgcn_ballot_w64(mx > m_ref[rb] + kLazyMaxSlack) != 0) {
-        mx = fmaxf(mx, __shfl_xor(mx, 16));
-        mx = fmaxf(mx, __shfl_xor(mx, 32));
-        const float mn = fmaxf(m_ref[rb], mx);
-        const float alpha = m_ref[rb] == -INFINITY ? 0.f : fast_exp2(m_ref[rb] - mn);
-        m_ref[rb] = mn;
-        l_sum[rb] *= alpha;
+  for (int db = 0; db < kDB; ++db)
 #pragma unroll
-        for (int db = 0; db < kDB; ++db) acc[rb][db] *= alpha;
-      }
-      uint2 p0, pl0, p1, pl1;
-      if (full) {
-        l_sum[rb] += weights4(S[rb][0], scale_log2, -m_ref[rb], p0, pl0) +
-                     weights4(S[rb][1], scale_log2, -m_ref[rb], p1, pl1);
-      } else {
-        l_sum[rb] += softmax_p4(x[0], m_ref[rb], p0, pl0) + softmax_p4(x[1], m_ref[rb], p1, pl1);
-      }
-      P[rb] = make_uint4(p0.x, p0.y, p1.x, p1.y);
-      PL[rb] = make_uint4(pl0.x, pl0.y, pl1.x, pl1.y);
+    for (int i = 0; i < 16; ++i) acc[db][i] = 0.f;
+  float m_ref = -INFINITY, l_sum = 0.f;
+  float neg_ref = 0.f;  // -m_ref once a score above -inf has been seen
+  f32x16 X;  // log2 weights of the current tile
+
+  auto qk = [&](int k) {
+    const char* kt = kbuf + (k & (kPfStages - 1)) * kHalf;
+    f32x16 S;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) S[i] = 0.f;
+    const int tok = pf_tau(r32);
+#pragma unroll
+    for (int ks = 0; ks < kKS; ++ks) {
+      const uint4 ka = *reinterpret_cast<const uint4*>(kt + tok * (D * 2) + (((2 * ks + half) ^ k_swz(tok)) << 4));
+      S = mfma32(ka, qb[ks], S);
     }
-    // one test per tile (not per d-block), so that the common full tile
-    // issues its V reads together and its MFMAs back to back
+    return S;
+  };
+  // Reference and log2 weights from the scores of the tile at `y` (its record's y).
+  auto weights = [&](f32x16 S, int y) {
+    const int first = y >> 6, cnt = y & 63;
+    if (!(cnt == kSub && first + kSub - 1 <= pos_lo)) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int t = 16 * (i >> 3) + 8 * half + (i & 7);
+        S[i] = t < cnt && first + t <= prow ? S[i] : -INFINITY;
+      }
+    }
+    float mx = S[0];
+#pragma unroll
+    for (int i = 1; i < 15; i += 2) mx = fmaxf(fmaxf(S[i], S[i + 1]), mx);
+    mx = fmaxf(mx, S[15]) * scale_log2;
+    if (__builtin_amdgcn_ballot_w64(mx > m_ref + kLazyMaxSlack) != 0) {
+      mx = fmaxf(mx, __shfl_xor(mx, 32));
+      const float mn = fmaxf(m_ref, mx);
+      const float alpha = m_ref == -INFINITY ? 0.f : fast_exp2(m_ref - mn);
+      m_ref = mn;
+      neg_ref = mn == -INFINITY ? 0.f : -mn;
+      l_sum *= alpha;
+#pragma unroll
+      for (int db = 0; db < kDB; ++db)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[db][i] *= alpha;
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) X[i] = fmaf(S[i], scale_log2, neg_ref);
+  };
+  // P of the lane's 8 tokens of k-step s as hi + lo bf16 terms
+  auto probs = [&](int s, uint4& P, uint4& PL) {
+    uint32_t ph[4], pl[4];
+    float ls = 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float f0 = fast_exp2(X[8 * s + 2 * e]), f1 = fast_exp2(X[8 * s + 2 * e + 1]);
+      const uint32_t hb = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){f0, f1}, bf16x2));
+      const float h0 = __builtin_bit_cast(float, hb << 16), h1 = __builtin_bit_cast(float, hb & 0xFFFF0000u);
+      pl[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){f0 - h0, f1 - h1}, bf16x2));
+      ph[e] = hb;
+      ls += f0 + f1;
+    }
+    l_sum += ls;
+    P = make_uint4(ph[0], ph[1], ph[2], ph[3]);
+    PL = make_uint4(pl[0], pl[1], pl[2], pl[3]);
+  };
+  auto pv = [&](int k, int s, const uint4& P, const uint4& PL) {
+    const char* vt = vbuf + (k & (kPfStages - 1)) * kHalf;
     uint4 va[kDB];
 #pragma unroll
     for (int db = 0; db < kDB; ++db) {
-      const int d = 16 * db + r16;
-      va[db] = *reinterpret_cast<const uint4*>(vt + d * (kSub * 2) + ((a ^ v_swz(d)) << 4));
+      const int d = 32 * db + r32;
+      va[db] = *reinterpret_cast<const uint4*>(vt + d * (kSub * 2) + (((2 * s + half) ^ v_swz(d)) << 4));
     }
-    if (cnt < kSub) {
 #pragma unroll
-      for (int db = 0; db < kDB; ++db) {
-        const uint2 lo = mask_v4(make_uint2(va[db].x, va[db].y), 8 * a, cnt);
-        const uint2 hi = mask_v4(make_uint2(va[db].z, va[db].w), 8 * a + 4, cnt);
-        va[db] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+    for (int db = 0; db < kDB; ++db) acc[db] = mfma32(va[db], P, acc[db]);
+#pragma unroll
+    for (int db = 0; db < kDB; ++db) acc[db] = mfma32(va[db], PL, acc[db]);
+  };
+  // Publishes group k (V of tile k, K of tile k + 1) and clears the V entries
+  // past a partial tile's tokens (their P is 0, but the pool may hold any bits
+  // there).  Every wave runs it for every tile.
+  int k = 0;
+  auto begin = [&]() {
+    barrier_tile_landed<2 * kPer * (kPfAhead - 1)>();
+    const int cnt = rec[0].y & 63;
+    if (cnt < kSub) {
+      uint16_t* vt = reinterpret_cast<uint16_t*>(vbuf + (k & (kPfStages - 1)) * kHalf);
+#pragma unroll 1
+      for (int i = threadIdx.x; i < D * kSub; i += 64 * W) {
+        const int d = i / kSub, t = i % kSub;
+        if (t >= cnt) vt[d * kSub + (((t >> 3) ^ v_swz(d)) << 3) + (t & 7)] = 0;
       }
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     }
+  };
+  // Group k + kPfAhead into the buffers that tile k - 1 (V) and k (K) used.
+  auto next_v = [&]() {
+    issue_v(rec[kPfAhead].x, (k + kPfAhead) & (kPfStages - 1), k + kPfAhead < nk ? ~0u : 0u);
+  };
+  auto next_k = [&]() {
+    issue_k(rec[kPfAhead + 1].x, (k + kPfAhead + 1) & (kPfStages - 1), k + kPfAhead + 1 < nk ? ~0u : 0u);
+  };
+  auto advance = [&]() {
+    ++k;
+#pragma unroll
+    for (int t = 0; t < kPfAhead + 1; ++t) rec[t] = rec[t + 1];
+    const int n = k + kPfAhead + 1;
+    rec[kPfAhead + 1] = tl[n < nk ? n : nk - 1];
+  };
+
+  barrier_tile_landed<2 * kPer * kPfAhead>();  // the query rows and K of tile 0
+  // Q^T operands: lane holds row 32 wave + r32, d chunk 2 ks + half
+#pragma unroll
+  for (int ks = 0; ks < kKS; ++ks)
+    qb[ks] = reinterpret_cast<const uint4*>(qbuf + wave * kQBytes)[r32 * kKChunks + ((2 * ks + half) ^ (r32 & (kKChunks - 1)))];
+  bool vis = wave_on;  // tile k holds keys of the wave's rows (tile 0 does)
+  if (vis) weights(qk(0), rec[0].y);
+  for (; k < nk; advance()) {
+    begin();
+    if (!vis) {
+      next_v();
+      next_k();
+      continue;
+    }
+    // QK of the next tile (unused, of whatever the buffer holds, when no tile
+    // follows) beside this tile's weights
+    const f32x16 S = qk(k + 1);
+    uint4 P, PL;
+    probs(0, P, PL);
+    next_v();
+    pv(k, 0, P, PL);
+    probs(1, P, PL);
+    next_k();
+    pv(k, 1, P, PL);
+    vis = k + 1 < nk && (rec[1].y >> 6) <= pos_hi;
+    if (vis) weights(S, rec[1].y);
+  }
+  barrier_tile_landed<0>();  // no load into this workgroup's LDS is left, and no wave reads a tile any more
+
+  // ---- normalised rows and their log-sum-exp: through the wave's share of
+  // the LDS, so that every store instruction writes whole rows (32 chunks of
+  // 16 bytes at D = 128; chunk c of row r at c ^ r)
+  float l = l_sum;
+  l += __shfl_xor(l, 32);
+  if (wave_on) {
+    constexpr int kCh = D / 4;         // 16-byte chunks of a row
+    constexpr int kRPI = 64 / kCh;     // rows per store instruction
+    const float inv = 1.f / l;
+    f32x4* ow = reinterpret_cast<f32x4*>(smem) + wave * 32 * kCh;
 #pragma unroll
     for (int db = 0; db < kDB; ++db)
 #pragma unroll
-      for (int rb = 0; rb < kRB; ++rb) acc[rb][db] = mfma16(va[db], PL[rb], mfma16(va[db], P[rb], acc[rb][db]));
-  };
-
-  // Software pipeline: iteration k scores tile k + 1 (its K) while it turns
-  // tile k's scores into weights and accumulates tile k's V, so the matrix
-  // cores work on QK while the vector ALUs do the softmax.  Tile k + 1 must
-  // have landed at the start of iteration k; two tiles stay in flight.
-  f32x4 Sc[kRB][2], Sn[kRB][2];
-  pp.wait(0, nk, 2);
-  int first_c = __builtin_amdgcn_readfirstlane(tl[0].y >> 6);
-  int cnt_c = __builtin_amdgcn_readfirstlane(tl[0].y & 63);
-  bool vis_c = wave_on && first_c <= pos_hi;
-  if (vis_c) qk(0, Sc);
-  for (int k = 0; k < nk; ++k) {
-    int first_n = 0, cnt_n = 0;
-    bool vis_n = false;
-    if (k + 1 < nk) {
-      pp.wait(k + 1, nk, 1);
-      if (k + kDepth < nk) {
-        pp.issue(kpool, vpool, hb_base + next.x, pp.buf0 + ((k + kDepth) & (kNBuf - 1)) * kBufBytes, wave);
-        if (k + kDepth + 1 < nk) next = tl[k + kDepth + 1];
-      }
-      const int2 rn = tl[k + 1];
-      first_n = __builtin_amdgcn_readfirstlane(rn.y >> 6);
-      cnt_n = __builtin_amdgcn_readfirstlane(rn.y & 63);
-      vis_n = wave_on && first_n <= pos_hi;
-    }
-    if (vis_n) qk(k + 1, Sn);
-    if (vis_c) softmax_pv(k, Sc, first_c, cnt_c);
+      for (int c = 0; c < 4; ++c)
+        ow[r32 * kCh + ((8 * db + 2 * c + half) ^ (r32 & (kCh - 1)))] =
+            f32x4{acc[db][4 * c], acc[db][4 * c + 1], acc[db][4 * c + 2], acc[db][4 * c + 3]} * inv;
+    const int n = it.n_rows - row_w;
+    float* op = out + (static_cast<int64_t>(it.row0 + row_w) * hq + h) * D + (lane % kCh) * 4;
 #pragma unroll
-    for (int rb = 0; rb < kRB; ++rb) {
-      Sc[rb][0] = Sn[rb][0];
-      Sc[rb][1] = Sn[rb][1];
+    for (int i = 0; i < 32 / kRPI; ++i) {
+      const int r = i * kRPI + lane / kCh;
+      const f32x4 v = ow[r * kCh + ((lane % kCh) ^ (r & (kCh - 1)))];
+      if (r < n) __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(op + static_cast<int64_t>(r) * hq * D));
     }
-    first_c = first_n;
-    cnt_c = cnt_n;
-    vis_c = vis_n;
-  }
-
-  // ---- normalised rows and their log-sum-exp
-#pragma unroll
-  for (int rb = 0; rb < kRB; ++rb) {
-    float l = l_sum[rb];
-    l += __shfl_xor(l, 16);
-    l += __shfl_xor(l, 32);
-    const int m = row_w + 16 * rb + r16;
-    if (wave_on && m < it.n_rows) {
-      const int64_t orow = static_cast<int64_t>(it.row0 + m) * hq + h;
-      const float inv = 1.f / l;
-#pragma unroll
-      for (int db = 0; db < kDB; ++db)
-        *reinterpret_cast<f32x4*>(out + orow * D + 16 * db + 4 * a) = acc[rb][db] * inv;
-      if (lse != nullptr && a == 0) lse[orow] = (m_ref[rb] + __log2f(l)) * kLn2;
-    }
+    if (lse != nullptr && half == 0 && r32 < n)
+      lse[static_cast<int64_t>(it.row0 + row_w + r32) * hq + h] = (m_ref + __log2f(l)) * kLn2;
   }
 }
 

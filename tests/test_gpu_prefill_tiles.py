@@ -1,0 +1,74 @@
+"""GPU parity of the prefill at the edges of its tiles: chains whose nodes end
+inside a 32-token tile, odd and even tile counts, items of one row, one wave
+and one row past an item, and scores of plus and minus infinity.
+
+Tolerance: the weights carry two bf16 terms (relative error 2^-17), so an
+output moves by at most 2^-17 of the largest |V| it averages (below 5.5 for the
+N(0, 1) rows here: 4.2e-5), and fp32 accumulation adds less than 1e-6.
+"""
+
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from oracle import prefill as PF
+from tests.test_gpu_prefill import _Rig
+
+TOL = 5e-5
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d,hq,hkv", [(128, 14, 2), (64, 6, 2)])
+@pytest.mark.parametrize("chain", [(1,), (31, 1), (32,), (33, 64, 95), (40, 45, 130)])
+def test_tile_edges(chain, d, hq, hkv):
+    rig = _Rig(hq, hkv, d, 7 + d + len(chain), num_blocks=400)
+    print(f"[prefill tiles chain={chain} d={d}]", flush=True)
+    x = rig.ctx.new_root(chain[0])
+    assert rig.model.new_root(chain[0]) == x
+    for i, n in enumerate(chain):
+        if i:
+            c = rig.ctx.fork(x, 1, n)
+            assert rig.model.fork(x, 1, n) == c
+            x = c[0]
+        qb, out, lse = rig.prefill([x], [n], i)
+        rig.check([x], [n], qb, out, lse, f"node {i}")
+    lens = [1, 32, 33, 128, 129]
+    kids = rig.ctx.fork(x, len(lens), 129)
+    assert rig.model.fork(x, len(lens), 129) == kids
+    qb, out, lse = rig.prefill(kids, lens, 50)
+    ref, ref_l = PF.prefill(rig.model, rig.node_kv, kids, lens, qb, rig.scale)
+    err, err_l = float(np.abs(out - ref).max()), float(np.abs(lse - ref_l).max())
+    print(f"max|out-oracle|={err:.3e} max|lse-oracle|={err_l:.3e}", flush=True)
+    assert err <= TOL and err_l <= TOL
+
+
+@pytest.mark.parametrize("sign", [1, -1])
+def test_infinite_scores(sign):
+    """A key of one token is infinite in column 0: rows before it are as
+    without it; for later rows its score is +inf (a NaN row) or -inf (weight
+    0), by the sign of the query's column 0."""
+    import torch
+    n, at, d = 70, 37, 64
+    rng = np.random.default_rng(3)
+    q, k, v = (torch.tensor(rng.standard_normal((n, 1, d)), dtype=torch.bfloat16) for _ in range(3))
+    q[:, 0, 0] = sign * q[:, 0, 0].abs().clamp(min=0.1)
+    k[at, 0, 0] = float("inf")
+    rig = _Rig(1, 1, d, 1, num_blocks=8)
+    x = rig.ctx.new_root(n)
+    out = torch.empty((n, 1, d), dtype=torch.float32, device="cuda")
+    lse = torch.empty((n, 1), dtype=torch.float32, device="cuda")
+    ws = torch.empty(rig.ctx.prefill_workspace_size([x], [n]), dtype=torch.uint8, device="cuda")
+    print(f"[prefill infinite scores sign={sign}]", flush=True)
+    rig.ctx.prefill([x], [n], q.cuda(), k.cuda(), v.cuda(), rig.scale, out, lse, ws)
+    torch.cuda.synchronize()
+    s = (q[:, 0].double() @ k[:, 0].double().T) * rig.scale
+    s = s.masked_fill(torch.triu(torch.ones(n, n, dtype=torch.bool), 1), float("-inf"))
+    ref = torch.softmax(s, -1) @ v[:, 0].double()
+    got = out[:, 0].cpu().double()
+    finite = torch.ones(n, dtype=torch.bool)
+    if sign > 0:
+        finite[at:] = False
+        assert torch.isnan(got[at:]).all() and torch.isnan(ref[at:]).all()
+    assert float((got[finite] - ref[finite]).abs().max()) <= TOL
