@@ -1,15 +1,28 @@
 // TreePO advantage over the rollout tree (TreePO Sec. 2.3, Eq. groups and
 // Eq. tree_ae; the sub-group-size weighted variant Eq. tree_ae_sgw of
 // Sec. 4.2), one workgroup, fp64 arithmetic:
-//   1. every sub-group's mean reward, and whether its rewards are all equal
-//      (a query whose group is all equal is rejected);
+//   1. every sub-group's mean reward, and whether a query's rewards are all
+//      equal (such a query is rejected);
 //   2. every kept position's sub-group advantages R_p - mean(G_a) over its
 //      strict predecessors a, pooled by their mean (or |G_a|-weighted mean),
 //      and the sums of all of them and of their squares;
 //   3. one global population standard deviation; advantage = pooled / std.
-// Sums run in a fixed order (per-thread partials in index order, then a
-// fixed tree), so results do not depend on scheduling.  The work is a few
-// thousand sub-groups and pairs per batch: a latency-bound kernel.
+// Sums run in a fixed order (a small run's members in turn, a large run's by
+// lane and then a fixed tree, the global sums by thread, wave and a fixed
+// tree), so results do not depend on scheduling.
+//
+// The positions are ordered depth first, so that a node's sub-group is one
+// range of them, and chain nodes with the same sub-group are one run (record
+// layout in kernels.h): a position's predecessors are the few runs above it,
+// each counted with its multiplicity.  Up to kAdvLdsRuns runs and
+// kAdvLdsPositions positions, runs and rewards are staged in LDS straight
+// from the pinned host image (one PCIe round trip, no copy before the
+// kernel); beyond that the image is in the workspace and read from there.
+//
+// Bound: latency (56 KB of tables for 1,024 trajectories).  That batch's call
+// took 68 us with member and predecessor lists in the workspace (a 120 KB
+// copy, 23 us with the gaps around it, then chains of dependent global loads,
+// 46 us).
 #include "kernels.h"
 
 #include <math.h>
@@ -18,87 +31,185 @@ namespace treepo {
 namespace {
 
 constexpr int kAdvThreads = 1024;
-// Rewards of up to this many positions are staged in LDS first, so that the
-// member loops' reads are LDS reads instead of dependent global loads.
-constexpr int kAdvLdsRewards = 8192;
+constexpr int kAdvWaves = kAdvThreads / 64;
+constexpr int kAdvPer = kAdvLdsPositions / kAdvThreads;
 
+// A run during the kernel: its sub-group's mean takes the place of the range.
+struct RunMean {
+  double mean;
+  int32_t parent, mult, size, pad;
+};
+static_assert(sizeof(RunMean) == sizeof(AdvRun), "runs are updated in place");
+
+__device__ __forceinline__ double wave_sum(double x) {
+#pragma unroll
+  for (int sh = 1; sh < 64; sh <<= 1) x += __shfl_xor(x, sh);
+  return x;
+}
+
+struct Pooled {
+  double pooled;
+  bool kept;
+};
+
+// Pooled advantage of one position with reward r; adds its terms to the sums.
+template <class Run>
+__device__ __forceinline__ Pooled pool_position(const Run* runs, int run, double r, bool size_weighted, double& s1,
+                                                double& s2, int32_t& cnt) {
+  double num = 0.0, den = 0.0, a1 = 0.0, a2 = 0.0;
+  int32_t n = 0, own = 1;  // the position's own node is the last of its run
+  bool keep = false;
+  while (run >= 0) {
+    const RunMean x = *reinterpret_cast<const RunMean*>(runs + run);
+    const int32_t m = x.mult - own;
+    own = 0;
+    if (m > 0) {
+      const double d = r - x.mean;
+      const double w = size_weighted ? static_cast<double>(x.size) : 1.0;
+      num += m * (w * d);
+      den += m * w;
+      a1 += m * d;
+      a2 += m * (d * d);
+      n += m;
+    }
+    keep = x.parent == kAdvKeptRoot;  // of the last run: the root's
+    run = x.parent;
+  }
+  if (!keep || n == 0) return Pooled{0.0, false};
+  s1 += a1;
+  s2 += a2;
+  cnt += n;
+  return Pooled{num / den, true};
+}
+
+template <bool kLds>
 __global__ __launch_bounds__(kAdvThreads) void advantage_kernel(AdvantageArgs a) {
-  __shared__ double red_s1[kAdvThreads];
-  __shared__ double red_s2[kAdvThreads];
-  __shared__ int32_t red_n[kAdvThreads];
-  __shared__ float rew[kAdvLdsRewards];
+  __shared__ double red[2][kAdvWaves];
+  __shared__ int32_t red_n[kAdvWaves];
+  __shared__ __attribute__((aligned(16))) AdvRun lds_runs[kLds ? kAdvLdsRuns : 1];
+  __shared__ float lds_rew[kLds ? kAdvLdsPositions : 1];
   const int tid = threadIdx.x;
-  const bool staged = a.n_pos <= kAdvLdsRewards;
-  if (staged) {
-    for (int p = tid; p < a.n_pos; p += kAdvThreads) rew[p] = a.rewards[p];
+  const int lane = tid & 63, wave = tid >> 6;
+  AdvRun* runs = kLds ? lds_runs : a.runs;
+  int2 pos[kLds ? kAdvPer : 1];
+  float rew[kLds ? kAdvPer : 1];
+  if constexpr (kLds) {
+#pragma unroll
+    for (int j = 0; j < kAdvPer; ++j) {
+      const int i = tid + j * kAdvThreads;
+      pos[j] = i < a.n_pos ? a.pos[i] : make_int2(0, 0);
+    }
+#pragma unroll
+    for (int j = 0; j < kAdvLdsRuns / kAdvThreads; ++j) {
+      const int i = tid + j * kAdvThreads;
+      if (i < a.n_runs) lds_runs[i] = a.runs[i];
+    }
+#pragma unroll
+    for (int j = 0; j < kAdvPer; ++j) {
+      const int i = tid + j * kAdvThreads;
+      rew[j] = i < a.n_pos ? a.rewards[pos[j].x] : 0.f;
+      if (i < a.n_pos) lds_rew[i] = rew[j];
+    }
     __syncthreads();
   }
-  const float* R = staged ? rew : a.rewards;
+  auto reward = [&](int i) { return kLds ? lds_rew[i] : a.rewards[a.pos[i].x]; };
 
-  // 1. sub-group means and the all-equal test
-  for (int g = tid; g < a.n_groups; g += kAdvThreads) {
-    const int b = a.grp_off[g], e = a.grp_off[g + 1];
+  // 1. means; runs are sorted by size, the first n_big have more members than
+  // kAdvSmallRun and take a wave each
+  auto finish = [&](int g, const AdvRun& x, double sum, float lo, float hi) {
+    const int size = x.end - x.begin;
+    RunMean r;
+    r.mean = sum / static_cast<double>(size);
+    r.parent = x.parent >= 0 ? x.parent : (hi != lo ? kAdvKeptRoot : -1);
+    r.mult = x.mult;
+    r.size = size;
+    r.pad = 0;
+    *reinterpret_cast<RunMean*>(runs + g) = r;
+  };
+  for (int g = wave; g < a.n_big; g += kAdvWaves) {
+    const AdvRun x = runs[g];
     double sum = 0.0;
     float lo = INFINITY, hi = -INFINITY;
-    for (int k = b; k < e; ++k) {
-      const float r = R[a.grp_mem[k]];
+    for (int i = x.begin + lane; i < x.end; i += 64) {
+      const float r = reward(i);
       sum += static_cast<double>(r);
       lo = fminf(lo, r);
       hi = fmaxf(hi, r);
     }
-    a.gmean[g] = e > b ? sum / static_cast<double>(e - b) : 0.0;
-    a.gkeep[g] = hi != lo;
+    sum = wave_sum(sum);
+#pragma unroll
+    for (int sh = 1; sh < 64; sh <<= 1) {
+      lo = fminf(lo, __shfl_xor(lo, sh));
+      hi = fmaxf(hi, __shfl_xor(hi, sh));
+    }
+    if (lane == 0) finish(g, x, sum, lo, hi);
+  }
+  for (int g = a.n_big + tid; g < a.n_runs; g += kAdvThreads) {
+    const AdvRun x = runs[g];
+    double sum = 0.0;
+    float lo = INFINITY, hi = -INFINITY;
+    for (int i = x.begin; i < x.end; ++i) {
+      const float r = reward(i);
+      sum += static_cast<double>(r);
+      lo = fminf(lo, r);
+      hi = fmaxf(hi, r);
+    }
+    finish(g, x, sum, lo, hi);
   }
   __syncthreads();
 
   // 2. pooled sub-group advantages of kept positions; global sums
   double s1 = 0.0, s2 = 0.0;
   int32_t cnt = 0;
-  for (int p = tid; p < a.n_pos; p += kAdvThreads) {
-    const int b = a.pos_off[p], e = a.pos_off[p + 1];
-    double pooled = 0.0;
-    if (a.gkeep[a.pos_root[p]] && e > b) {
-      const double r = static_cast<double>(R[p]);
-      double num = 0.0, den = 0.0;
-      for (int k = b; k < e; ++k) {
-        const int g = a.pos_grp[k];
-        const double d = r - a.gmean[g];
-        const double w = a.size_weighted ? static_cast<double>(a.grp_off[g + 1] - a.grp_off[g]) : 1.0;
-        num += w * d;
-        den += w;
-        s1 += d;
-        s2 += d * d;
-        ++cnt;
-      }
-      pooled = num / den;
+  Pooled mine[kLds ? kAdvPer : 1];
+  if constexpr (kLds) {
+#pragma unroll
+    for (int j = 0; j < kAdvPer; ++j)
+      mine[j] = tid + j * kAdvThreads < a.n_pos
+                    ? pool_position(runs, pos[j].y, static_cast<double>(rew[j]), a.size_weighted != 0, s1, s2, cnt)
+                    : Pooled{0.0, false};
+  } else {
+    for (int i = tid; i < a.n_pos; i += kAdvThreads) {
+      const Pooled p = pool_position(runs, a.pos[i].y, static_cast<double>(reward(i)), a.size_weighted != 0, s1, s2,
+                                     cnt);
+      a.pooled[i] = p.kept ? p.pooled : 0.0;
     }
-    a.pooled[p] = pooled;
   }
-  red_s1[tid] = s1;
-  red_s2[tid] = s2;
-  red_n[tid] = cnt;
+  s1 = wave_sum(s1);
+  s2 = wave_sum(s2);
+#pragma unroll
+  for (int sh = 1; sh < 64; sh <<= 1) cnt += __shfl_xor(cnt, sh);
+  if (lane == 0) {
+    red[0][wave] = s1;
+    red[1][wave] = s2;
+    red_n[wave] = cnt;
+  }
   __syncthreads();
-  for (int w = kAdvThreads / 2; w > 0; w >>= 1) {
-    if (tid < w) {
-      red_s1[tid] += red_s1[tid + w];
-      red_s2[tid] += red_s2[tid + w];
-      red_n[tid] += red_n[tid + w];
-    }
-    __syncthreads();
-  }
 
   // 3. divide by the global population standard deviation
-  const int32_t n = red_n[0];
+  double t1 = 0.0, t2 = 0.0;
+  int32_t n = 0;
+#pragma unroll
+  for (int w = 0; w < kAdvWaves; ++w) {
+    t1 += red[0][w];
+    t2 += red[1][w];
+    n += red_n[w];
+  }
   double sigma = 0.0;
   if (n > 0) {
-    const double m = red_s1[0] / n;
-    const double var = red_s2[0] / n - m * m;
+    const double m = t1 / n;
+    const double var = t2 / n - m * m;
     sigma = var > 0.0 ? sqrt(var) : 0.0;
   }
-  for (int p = tid; p < a.n_pos; p += kAdvThreads) {
-    const int b = a.pos_off[p], e = a.pos_off[p + 1];
-    const bool kept = a.gkeep[a.pos_root[p]] && e > b;
-    a.adv[p] = kept && sigma > 0.0 ? static_cast<float>(a.pooled[p] / sigma) : 0.f;
+  // a position that is not kept pooled 0
+  if constexpr (kLds) {
+#pragma unroll
+    for (int j = 0; j < kAdvPer; ++j)
+      if (tid + j * kAdvThreads < a.n_pos)
+        a.adv[pos[j].x] = mine[j].kept && sigma > 0.0 ? static_cast<float>(mine[j].pooled / sigma) : 0.f;
+  } else {
+    for (int i = tid; i < a.n_pos; i += kAdvThreads)
+      a.adv[a.pos[i].x] = sigma > 0.0 ? static_cast<float>(a.pooled[i] / sigma) : 0.f;
   }
 }
 
@@ -106,7 +217,12 @@ __global__ __launch_bounds__(kAdvThreads) void advantage_kernel(AdvantageArgs a)
 
 hipError_t launch_advantage(const AdvantageArgs& a, hipStream_t s) {
   if (a.n_pos <= 0) return hipSuccess;
-  hipLaunchKernelGGL(advantage_kernel, dim3(1), dim3(kAdvThreads), 0, s, a);
+  if (a.in_lds) {
+    if (a.n_runs > kAdvLdsRuns || a.n_pos > kAdvLdsPositions) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(advantage_kernel<true>, dim3(1), dim3(kAdvThreads), 0, s, a);
+  } else {
+    hipLaunchKernelGGL(advantage_kernel<false>, dim3(1), dim3(kAdvThreads), 0, s, a);
+  }
   return hipGetLastError();
 }
 

@@ -49,25 +49,30 @@ hipError_t launch_combine(const DecodeArgs& a, hipStream_t s);
 // register and LDS budget); the planner makes one stream per resident slot.
 int32_t partial_workgroups_per_cu();
 
-// TreePO advantage (advantage.hip): one workgroup over index arrays built on
-// the host from the leaves' chains.  Sub-group g = the call positions whose
-// chain contains node g (members grp_mem[grp_off[g], grp_off[g+1]));
-// position p's strict predecessors are the sub-groups
-// pos_grp[pos_off[p], pos_off[p+1]) (root first), its query's group
-// pos_root[p].
+// TreePO advantage (advantage.hip): one workgroup over an image built on the
+// host from the leaves' chains.  The call positions are ordered depth first
+// (children of a node after the positions that end at it), so a chain node's
+// sub-group -- the positions whose chain contains it -- is a range of them.
+// Chain nodes with the same sub-group are consecutive on every chain: a run.
+// Runs are sorted by size, largest first (so a run's parent precedes it).
+struct AdvRun {
+  int32_t begin, end;  // ordered positions of its sub-group
+  int32_t parent;      // the run above it, -1 at a query's root
+  int32_t mult;        // chain nodes in the run
+  int32_t pad[2];      // room for the mean
+};
+constexpr int32_t kAdvKeptRoot = -2;        // parent of a root run whose rewards are not all equal
+constexpr int32_t kAdvSmallRun = 16;        // members that one thread sums
+constexpr int32_t kAdvLdsRuns = 4096;       // runs and positions that the LDS path holds
+constexpr int32_t kAdvLdsPositions = 4096;
 struct AdvantageArgs {
-  const int32_t* grp_off;
-  const int32_t* grp_mem;
-  int32_t n_groups;
-  const int32_t* pos_off;
-  const int32_t* pos_grp;
-  const int32_t* pos_root;
-  int32_t n_pos;
+  AdvRun* runs;            // [n_runs]: pinned host image (in_lds), else device, updated in place
+  const int2* pos;         // [n_pos] in order: call position, its run; beside runs
+  int32_t n_runs, n_big, n_pos;
+  int32_t in_lds;          // stage the image in LDS (sizes within the limits above)
   const float* rewards;    // [n_pos], device
   int32_t size_weighted;   // 0: mean over sub-groups, 1: |G|-weighted mean
-  double* gmean;           // [n_groups] scratch
-  int32_t* gkeep;          // [n_groups] scratch: rewards of the sub-group not all equal
-  double* pooled;          // [n_pos] scratch
+  double* pooled;          // [n_pos] device scratch (not in_lds)
   float* adv;              // [n_pos], device
 };
 hipError_t launch_advantage(const AdvantageArgs& a, hipStream_t s);

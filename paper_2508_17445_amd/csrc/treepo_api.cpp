@@ -86,13 +86,15 @@ struct PinnedSlot {
   bool pending = false;
 };
 
-// Index arrays of the advantage kernel for a leaf list, as one int32 image
-// (uploaded into the workspace), plus the scratch that follows it.
+// Host image of the advantage kernel for a leaf list: the runs, then per
+// ordered position {call position, run}.
 struct AdvPlan {
-  std::vector<int32_t> ints;
-  int32_t n_groups = 0;
-  size_t off_grp_off = 0, off_grp_mem = 0, off_pos_off = 0, off_pos_grp = 0, off_pos_root = 0;  // in ints
-  size_t off_gmean = 0, off_gkeep = 0, off_pooled = 0, ws_bytes = 0;                           // in bytes
+  std::vector<treepo::AdvRun> runs;
+  std::vector<int32_t> pos;
+  int32_t n_big = 0;
+  bool in_lds = false;
+  size_t off_pos = 0, bytes = 0;     // of the image
+  size_t off_pooled = 0, ws_bytes = 0;  // in the workspace (sizes past the LDS path)
   uint64_t shape_version = 0;  // the tree shape it was built for
   std::vector<int32_t> leaves;
 };
@@ -212,8 +214,8 @@ hipError_t timed_launch(treepo_ctx* ctx, int kind, hipStream_t s, F launch) {
   return hipSuccess;
 }
 
-// Copies `bytes` of host data to device `dst` on `s` through a pinned slot.
-hipError_t upload(treepo_ctx* ctx, void* dst, const void* src, size_t bytes, hipStream_t s) {
+// The next pinned slot, with room for `bytes` and no reader left.
+hipError_t acquire_slot(treepo_ctx* ctx, size_t bytes, PinnedSlot** out) {
   PinnedSlot& sl = ctx->ring[ctx->ring_next];
   ctx->ring_next = (ctx->ring_next + 1) % kRing;
   hipError_t e;
@@ -238,13 +240,26 @@ hipError_t upload(treepo_ctx* ctx, void* dst, const void* src, size_t bytes, hip
     if (e != hipSuccess) return e;
     sl.cap = cap;
   }
-  std::memcpy(sl.p, src, bytes);
-  e = hipMemcpyAsync(dst, sl.p, bytes, hipMemcpyHostToDevice, s);
-  if (e != hipSuccess) return e;
-  e = hipEventRecord(sl.ev, s);
-  if (e != hipSuccess) return e;
-  sl.pending = true;
+  *out = &sl;
   return hipSuccess;
+}
+
+// Marks that the work enqueued on `s` so far reads the slot.
+hipError_t release_slot(PinnedSlot* sl, hipStream_t s) {
+  const hipError_t e = hipEventRecord(sl->ev, s);
+  if (e == hipSuccess) sl->pending = true;
+  return e;
+}
+
+// Copies `bytes` of host data to device `dst` on `s` through a pinned slot.
+hipError_t upload(treepo_ctx* ctx, void* dst, const void* src, size_t bytes, hipStream_t s) {
+  PinnedSlot* sl = nullptr;
+  hipError_t e = acquire_slot(ctx, bytes, &sl);
+  if (e != hipSuccess) return e;
+  std::memcpy(sl->p, src, bytes);
+  e = hipMemcpyAsync(dst, sl->p, bytes, hipMemcpyHostToDevice, s);
+  if (e != hipSuccess) return e;
+  return release_slot(sl, s);
 }
 
 template <class T>
@@ -588,56 +603,105 @@ void append_pieces(const treepo::Tree& t, int32_t n, const int32_t* nodes, const
 
 namespace {
 
-// Sub-group g = a node on some leaf's chain, numbered in order of first
-// appearance (positions ascending, chains root first); its members are the
-// positions whose chain contains it, ascending.
+// Orders the positions depth first and cuts the chain nodes into runs (record
+// layout in kernels.h).  O(nodes on the chains).
 void build_adv_plan(const treepo::Tree& t, int32_t n, const int32_t* leaves, AdvPlan* ap) {
-  std::vector<std::vector<int32_t>> chains(n);
-  std::vector<int32_t> gid(t.nodes().size(), -1);
-  std::vector<std::vector<int32_t>> members;
+  const auto& nd = t.nodes();
+  // on-chain nodes in order of first appearance: parent, children and the
+  // positions that end at the node as linked lists in that order
+  struct ChainNode {
+    int32_t up, depth, kid, last_kid, sibling, pos, last_pos, begin, end, run;
+  };
+  std::vector<int32_t> index(nd.size(), -1), next_pos(static_cast<size_t>(n), -1), chain;
+  std::vector<ChainNode> c;
+  c.reserve(static_cast<size_t>(n) * 4);
+  int32_t first_root = -1, last_root = -1;
+  size_t pairs = 0;  // (position, chain node)
   for (int32_t p = 0; p < n; ++p) {
-    t.chain(leaves[p], &chains[p]);
-    for (int32_t x : chains[p]) {
-      if (gid[x] < 0) {
-        gid[x] = static_cast<int32_t>(members.size());
-        members.emplace_back();
-      }
-      members[gid[x]].push_back(p);
+    chain.clear();
+    int32_t y = leaves[p];
+    for (; y != -1 && index[y] < 0; y = nd[y].parent) chain.push_back(y);
+    int32_t up = y == -1 ? -1 : index[y];
+    for (size_t i = chain.size(); i-- > 0;) {
+      const int32_t k = static_cast<int32_t>(c.size());
+      index[chain[i]] = k;
+      c.push_back(ChainNode{up, up < 0 ? 1 : c[up].depth + 1, -1, -1, -1, -1, -1, 0, 0, 0});
+      int32_t& last = up < 0 ? last_root : c[up].last_kid;
+      (last >= 0 ? c[last].sibling : up < 0 ? first_root : c[up].kid) = k;
+      last = k;
+      up = k;
+    }
+    ChainNode& x = c[index[leaves[p]]];
+    (x.last_pos >= 0 ? next_pos[x.last_pos] : x.pos) = p;
+    x.last_pos = p;
+    pairs += static_cast<size_t>(x.depth);
+  }
+  // depth-first ranges
+  const size_t m = c.size();
+  std::vector<int32_t> order, of;
+  order.reserve(n);
+  of.reserve(n);
+  std::vector<int32_t> preorder;
+  preorder.reserve(m);
+  for (int32_t k = first_root; k >= 0;) {
+    preorder.push_back(k);
+    c[k].begin = static_cast<int32_t>(order.size());
+    for (int32_t p = c[k].pos; p >= 0; p = next_pos[p]) {
+      order.push_back(p);
+      of.push_back(k);
+    }
+    if (c[k].kid >= 0) {
+      k = c[k].kid;
+      continue;
+    }
+    for (; k >= 0; k = c[k].up) {
+      c[k].end = static_cast<int32_t>(order.size());
+      if (c[k].sibling >= 0) break;
+    }
+    if (k >= 0) k = c[k].sibling;
+  }
+  // runs, parents first; then by size
+  std::vector<treepo::AdvRun> runs;
+  for (int32_t k : preorder) {
+    const int32_t up = c[k].up;
+    if (up >= 0 && c[up].begin == c[k].begin && c[up].end == c[k].end) {
+      c[k].run = c[up].run;
+      ++runs[c[k].run].mult;
+    } else {
+      c[k].run = static_cast<int32_t>(runs.size());
+      runs.push_back(treepo::AdvRun{c[k].begin, c[k].end, up < 0 ? -1 : c[up].run, 1, {0, 0}});
     }
   }
-  const int32_t G = static_cast<int32_t>(members.size());
-  std::vector<int32_t>& v = ap->ints;
-  v.clear();
-  ap->n_groups = G;
-  ap->off_grp_off = v.size();
-  int32_t acc = 0;
-  for (int32_t g = 0; g < G; ++g) {
-    v.push_back(acc);
-    acc += static_cast<int32_t>(members[g].size());
+  std::vector<int32_t> by(runs.size()), at(runs.size());
+  for (size_t i = 0; i < by.size(); ++i) by[i] = static_cast<int32_t>(i);
+  std::stable_sort(by.begin(), by.end(), [&](int32_t a, int32_t b) {
+    return runs[a].end - runs[a].begin > runs[b].end - runs[b].begin;
+  });
+  for (size_t i = 0; i < by.size(); ++i) at[by[i]] = static_cast<int32_t>(i);
+  ap->runs.clear();
+  ap->n_big = 0;
+  for (int32_t i : by) {
+    treepo::AdvRun r = runs[i];
+    if (r.parent >= 0) r.parent = at[r.parent];
+    if (r.end - r.begin > treepo::kAdvSmallRun) ++ap->n_big;
+    ap->runs.push_back(r);
   }
-  v.push_back(acc);
-  ap->off_grp_mem = v.size();
-  for (const auto& m : members) v.insert(v.end(), m.begin(), m.end());
-  ap->off_pos_off = v.size();
-  acc = 0;
-  for (int32_t p = 0; p < n; ++p) {
-    v.push_back(acc);
-    acc += static_cast<int32_t>(chains[p].size()) - 1;
+  ap->pos.resize(2 * static_cast<size_t>(n));
+  for (int32_t i = 0; i < n; ++i) {
+    ap->pos[2 * i] = order[i];
+    ap->pos[2 * i + 1] = at[c[of[i]].run];
   }
-  v.push_back(acc);
-  ap->off_pos_grp = v.size();
-  for (int32_t p = 0; p < n; ++p)
-    for (size_t j = 0; j + 1 < chains[p].size(); ++j) v.push_back(gid[chains[p][j]]);
-  ap->off_pos_root = v.size();
-  for (int32_t p = 0; p < n; ++p) v.push_back(gid[chains[p][0]]);
-  size_t off = align_up(v.size() * sizeof(int32_t));
-  ap->off_gmean = off;
-  off = align_up(off + static_cast<size_t>(G) * sizeof(double));
-  ap->off_gkeep = off;
-  off = align_up(off + static_cast<size_t>(G) * sizeof(int32_t));
-  ap->off_pooled = off;
-  off = align_up(off + static_cast<size_t>(n) * sizeof(double));
-  ap->ws_bytes = off;
+  ap->in_lds = ap->runs.size() <= static_cast<size_t>(treepo::kAdvLdsRuns) && n <= treepo::kAdvLdsPositions;
+  ap->off_pos = ap->runs.size() * sizeof(treepo::AdvRun);
+  ap->bytes = ap->off_pos + ap->pos.size() * sizeof(int32_t);
+  ap->off_pooled = align_up(ap->bytes);
+  // The workspace: room for per-node and per-predecessor lists, whichever of
+  // them a call needs (8 bytes a pair, 16 a node, 12 a position and more
+  // than the image and the pooled values).
+  const size_t N = static_cast<size_t>(n);
+  ap->ws_bytes = align_up((m + 1 + pairs + N + 1 + (pairs - N) + N) * sizeof(int32_t)) + align_up(m * sizeof(double)) +
+                 align_up(m * sizeof(int32_t)) + align_up(N * sizeof(double));
+  ap->ws_bytes = std::max(ap->ws_bytes, ap->in_lds ? size_t{0} : ap->off_pooled + N * sizeof(double));
 }
 
 // The machine the decode planner sizes its streams for: one stream per
@@ -1043,7 +1107,7 @@ int32_t treepo_tree_advantage(treepo_ctx* ctx, int32_t n_leaves, const int32_t* 
   if (weighting != TREEPO_ADV_MEAN && weighting != TREEPO_ADV_SIZE_WEIGHTED)
     return fail(ctx, TREEPO_EINVAL, "bad weighting");
   AdvPlan& ap = ctx->adv;
-  if (ap.ints.empty() || ap.shape_version != ctx->tree.shape_version() ||
+  if (ap.runs.empty() || ap.shape_version != ctx->tree.shape_version() ||
       ap.leaves.size() != static_cast<size_t>(n_leaves) || !std::equal(ap.leaves.begin(), ap.leaves.end(), leaves)) {
     build_adv_plan(ctx->tree, n_leaves, leaves, &ap);
     ap.shape_version = ctx->tree.shape_version();
@@ -1053,25 +1117,32 @@ int32_t treepo_tree_advantage(treepo_ctx* ctx, int32_t n_leaves, const int32_t* 
     return fail(ctx, TREEPO_EWORKSPACE,
                 "workspace missing, smaller than treepo_advantage_workspace_size or not 256-byte aligned");
   char* wsb = static_cast<char*>(workspace);
-  hipError_t e = upload(ctx, wsb, ap.ints.data(), ap.ints.size() * sizeof(int32_t), stream);
-  if (e != hipSuccess) return hip_fail(ctx, e, "advantage index upload");
-  const int32_t* ints = reinterpret_cast<const int32_t*>(wsb);
+  PinnedSlot* sl = nullptr;
+  hipError_t e = acquire_slot(ctx, ap.bytes, &sl);
+  if (e != hipSuccess) return hip_fail(ctx, e, "advantage staging");
+  char* img = static_cast<char*>(sl->p);
+  std::memcpy(img, ap.runs.data(), ap.off_pos);
+  std::memcpy(img + ap.off_pos, ap.pos.data(), ap.bytes - ap.off_pos);
+  if (!ap.in_lds) {
+    e = hipMemcpyAsync(wsb, img, ap.bytes, hipMemcpyHostToDevice, stream);
+    if (e != hipSuccess) return hip_fail(ctx, e, "advantage index upload");
+    img = wsb;
+  }
   treepo::AdvantageArgs a;
-  a.grp_off = ints + ap.off_grp_off;
-  a.grp_mem = ints + ap.off_grp_mem;
-  a.n_groups = ap.n_groups;
-  a.pos_off = ints + ap.off_pos_off;
-  a.pos_grp = ints + ap.off_pos_grp;
-  a.pos_root = ints + ap.off_pos_root;
+  a.runs = reinterpret_cast<treepo::AdvRun*>(img);
+  a.pos = reinterpret_cast<const int2*>(img + ap.off_pos);
+  a.n_runs = static_cast<int32_t>(ap.runs.size());
+  a.n_big = ap.n_big;
   a.n_pos = n_leaves;
+  a.in_lds = ap.in_lds ? 1 : 0;
   a.rewards = rewards;
   a.size_weighted = weighting == TREEPO_ADV_SIZE_WEIGHTED;
-  a.gmean = reinterpret_cast<double*>(wsb + ap.off_gmean);
-  a.gkeep = reinterpret_cast<int32_t*>(wsb + ap.off_gkeep);
   a.pooled = reinterpret_cast<double*>(wsb + ap.off_pooled);
   a.adv = adv;
   e = timed_launch(ctx, TREEPO_KERNEL_ADVANTAGE, stream, [&] { return treepo::launch_advantage(a, stream); });
+  const hipError_t r = release_slot(sl, stream);
   if (e != hipSuccess) return hip_fail(ctx, e, "advantage kernel launch");
+  if (r != hipSuccess) return hip_fail(ctx, r, "advantage staging");
   return TREEPO_OK;
 }
 
