@@ -728,7 +728,7 @@ def _summarize_prefill(cfg_id, d):
         return f"{len(v)} | {statistics.mean(v):.2f} | {statistics.median(v):.2f} | {min(v):.2f} | {max(v):.2f}"
 
     pf = [r for r in rows if "prefill_kernel" in r["Kernel_Name"]]
-    ap = [dur(r) for r in rows if "kv_append_dev_kernel" in r["Kernel_Name"]]
+    ap = [dur(r) for r in rows if "prefill_append_kernel" in r["Kernel_Name"]]
     warm, steps = b["warmup"], b["steps"]
     timed = pf[warm:warm + steps]
     flops = b["roofline"]["algorithmic_flops_per_launch"]
@@ -754,7 +754,7 @@ per-rollout baseline's).
 | kernel | grid (threads) | dispatches | avg us | median us | min us | max us |
 |---|---|---|---|---|---|---|
 | prefill_kernel<{cfg.d}>, timed steps | {grid} | {stats([dur(r) for r in timed])} |
-| kv_append_dev_kernel<{cfg.d}> (all calls) | - | {stats(ap)} |
+| prefill_append_kernel<{cfg.d}> (all calls) | - | {stats(ap)} |
 
 Algorithmic FLOPs per launch (causal QK and PV, 4 D flops per query-key pair
 and query head): {flops} -> {flops / (avg * 1e-6) / 1e12:.1f} TFLOP/s on the

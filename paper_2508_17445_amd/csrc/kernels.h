@@ -125,11 +125,26 @@ hipError_t launch_kv_append(const uint16_t* k_src, const uint16_t* v_src, uint16
                             uint16_t* v_pool, int64_t pool_rows, int32_t hkv, int32_t d,
                             const AppendPiece* pieces, int32_t n_pieces, const int32_t* upd_node,
                             const int32_t* upd_len, int32_t n_upd, int32_t* node_len, hipStream_t s);
-// The same with pieces and updates (x = node, y = length) in device memory,
-// in one launch.
-hipError_t launch_kv_append_dev(const uint16_t* k_src, const uint16_t* v_src, uint16_t* k_pool, uint16_t* v_pool,
-                                int64_t pool_rows, int32_t hkv, int32_t d, const AppendPiece* pieces,
-                                int32_t n_pieces, const int2* upd, int32_t n_upd, int32_t* node_len,
-                                hipStream_t s);
+// The append of a prefill, in one launch that also moves the attention tables:
+// `image` (pinned host memory) holds table_bytes (a multiple of 16) of them,
+// copied to `tables` (device); pieces and updates (x = node, y = length) lie
+// in the image too.
+struct PrefillAppendArgs {
+  const uint16_t* k_src;
+  const uint16_t* v_src;
+  uint16_t* k_pool;
+  uint16_t* v_pool;
+  int64_t pool_rows;
+  int32_t hkv, d;
+  int32_t* node_len;  // or null
+  const AppendPiece* pieces;
+  int32_t n_pieces;
+  const int2* upd;
+  int32_t n_upd;
+  const void* image;
+  void* tables;
+  size_t table_bytes;
+};
+hipError_t launch_prefill_append(const PrefillAppendArgs& a, hipStream_t s);
 
 }  // namespace treepo

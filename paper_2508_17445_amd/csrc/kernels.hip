@@ -992,9 +992,13 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(const int2* __restric
 // ---- KV append --------------------------------------------------------------
 //
 // One workgroup per (piece, KV head).  K rows are copied with 16-byte moves;
-// V rows are transposed through LDS (padded rows, no bank conflicts) and
-// written as runs of consecutive tokens of each d-row of the transposed
-// 16-row groups.
+// V rows are transposed through LDS into the pool's [D][16] groups: a thread
+// takes two d-rows of 8 consecutive tokens -- 8 dword reads (rows padded to
+// D + 8 elements: no bank conflicts), two 16-byte stores -- or, where the
+// piece covers the 8 tokens in part, the 2-byte entries that it holds.  Bound
+// by memory: the rows of 64 prompts of 256-1024 tokens (4 KV heads of D 128,
+// 169 MB read and written) took 45 us with 2-byte stores and one row chunk in
+// flight per thread, kMeasuredBatch us now.
 constexpr int kMaxPieces = 128;
 struct AppendBatch {
   int32_t n;      // pieces
@@ -1003,34 +1007,68 @@ struct AppendBatch {
   int2 upd[kMaxPieces];
 };
 
-// One piece for KV head blockIdx.y: K rows copied with 16-byte moves, V
-// transposed through padded LDS into the pool's [D][16] groups.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+template <int D>
+constexpr int append_lds_dwords() { return kTile * (D + 8) / 2; }
+
+// One piece for KV head g.
 template <int D>
 __device__ __forceinline__ void append_piece(const uint16_t* __restrict__ ksrc, const uint16_t* __restrict__ vsrc,
                                              uint16_t* __restrict__ kpool, uint16_t* __restrict__ vpool,
-                                             int64_t rows, int32_t hkv, const AppendPiece& pc, uint16_t* vt) {
-  constexpr int kPad = D + 2;
-  const int g = blockIdx.y;
-  const int64_t row0 = static_cast<int64_t>(g) * rows + static_cast<int64_t>(pc.block) * kTile + pc.off;
+                                             int64_t rows, int32_t hkv, int g, const AppendPiece& pc, uint32_t* vt) {
+  constexpr int kRow = (D + 8) / 2;  // dwords of an LDS row
   constexpr int kCh = D / 8;
-  for (int idx = threadIdx.x; idx < pc.count * kCh; idx += kThreads) {
-    const int i = idx / kCh, c = idx % kCh;
-    const int64_t src = (static_cast<int64_t>(pc.src_row + i) * hkv + g) * D + c * 8;
-    const uint4 kvv = *reinterpret_cast<const uint4*>(ksrc + src);
-    *reinterpret_cast<uint4*>(kpool + (row0 + i) * D + c * 8) = kvv;
-    const uint4 vv = *reinterpret_cast<const uint4*>(vsrc + src);
-    const uint32_t w[4] = {vv.x, vv.y, vv.z, vv.w};
+  constexpr int kIter = kTile * kCh / kThreads;
+  const int tid = threadIdx.x;
+  const int64_t row0 = static_cast<int64_t>(g) * rows + static_cast<int64_t>(pc.block) * kTile + pc.off;
+  u32x4 kk[kIter], vv[kIter];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      vt[i * kPad + c * 8 + 2 * e] = static_cast<uint16_t>(w[e] & 0xFFFFu);
-      vt[i * kPad + c * 8 + 2 * e + 1] = static_cast<uint16_t>(w[e] >> 16);
+  for (int j = 0; j < kIter; ++j) {
+    const int i = (tid + j * kThreads) / kCh, c = tid % kCh;
+    if (i < pc.count) {
+      const int64_t src = (static_cast<int64_t>(pc.src_row + i) * hkv + g) * D + c * 8;
+      kk[j] = *reinterpret_cast<const u32x4*>(ksrc + src);
+      vv[j] = *reinterpret_cast<const u32x4*>(vsrc + src);
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < kIter; ++j) {
+    const int i = (tid + j * kThreads) / kCh, c = tid % kCh;
+    if (i < pc.count) {
+      *reinterpret_cast<u32x4*>(kpool + (row0 + i) * D + c * 8) = kk[j];
+      *reinterpret_cast<u32x4*>(vt + i * kRow + c * 4) = vv[j];
     }
   }
   __syncthreads();
-  for (int idx = threadIdx.x; idx < D * pc.count; idx += kThreads) {
-    const int d = idx / pc.count, i = idx % pc.count;
-    const int64_t p = row0 + i;  // pool row (KV head included; g * rows is a multiple of 16)
-    vpool[(p / kVGroup) * kVGroup * D + d * kVGroup + p % kVGroup] = vt[i * kPad + d];
+  const int a0 = pc.off % kVGroup;  // the first row's place in its 16-row group
+  uint16_t* const vg = vpool + (row0 - a0) * D;
+  const int n = (a0 + pc.count + kVGroup - 1) / kVGroup * D;
+  for (int idx = tid; idx < n; idx += kThreads) {
+    const int grp = idx / D, half = idx & 1, dp = (idx % D) >> 1;
+    const int t0 = grp * kVGroup + half * 8 - a0;  // the piece's row of the first of the 8 tokens
+    uint16_t* const dst = vg + grp * kVGroup * D + dp * 2 * kVGroup + half * 8;
+    if (t0 >= 0 && t0 + 8 <= pc.count) {
+      uint32_t w[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) w[e] = vt[(t0 + e) * kRow + dp];
+      u32x4 lo, hi;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        lo[e] = (w[2 * e] & 0xFFFFu) | (w[2 * e + 1] << 16);
+        hi[e] = (w[2 * e] >> 16) | (w[2 * e + 1] & 0xFFFF0000u);
+      }
+      *reinterpret_cast<u32x4*>(dst) = lo;
+      *reinterpret_cast<u32x4*>(dst + kVGroup) = hi;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        if (t0 + e < 0 || t0 + e >= pc.count) continue;
+        const uint32_t w = vt[(t0 + e) * kRow + dp];
+        dst[e] = static_cast<uint16_t>(w);
+        dst[kVGroup + e] = static_cast<uint16_t>(w >> 16);
+      }
+    }
   }
 }
 
@@ -1042,30 +1080,51 @@ __global__ __launch_bounds__(kThreads) void kv_append_kernel(const uint16_t* __r
                                                              uint16_t* __restrict__ vpool,
                                                              int64_t rows, int32_t hkv,
                                                              int32_t* __restrict__ node_len, AppendBatch b) {
-  __shared__ uint16_t vt[kTile * (D + 2)];
+  __shared__ __attribute__((aligned(16))) uint32_t vt[append_lds_dwords<D>()];
   if (node_len != nullptr && blockIdx.y == 0 && threadIdx.x == 0 && static_cast<int>(blockIdx.x) < b.n_upd)
     node_len[b.upd[blockIdx.x].x] = b.upd[blockIdx.x].y;
   if (static_cast<int>(blockIdx.x) >= b.n) return;
-  append_piece<D>(ksrc, vsrc, kpool, vpool, rows, hkv, b.p[blockIdx.x], vt);
+  append_piece<D>(ksrc, vsrc, kpool, vpool, rows, hkv, blockIdx.y, b.p[blockIdx.x], vt);
 }
 
-// The same with the pieces and length updates in device memory: one launch
-// for any number of pieces.
+// The append of a prefill, and its tables.  The host writes one image (pinned
+// memory): the attention kernel's tables, then this kernel's pieces and
+// length updates.  The first n_copy workgroups copy the tables to the
+// workspace, 16 KiB each, and write the lengths; the others take one piece
+// each, read straight from the image.  A separate copy of the image costs a
+// switch of engines on either side: 17 us for one prompt of 513 tokens, 40 us
+// for the 64 above (copy 4-7 us, the rest gaps).
+constexpr int kCopyPer = 4;  // 16-byte loads per thread of a copying workgroup
 template <int D>
-__global__ __launch_bounds__(kThreads) void kv_append_dev_kernel(
+__global__ __launch_bounds__(kThreads) void prefill_append_kernel(
     const uint16_t* __restrict__ ksrc, const uint16_t* __restrict__ vsrc, uint16_t* __restrict__ kpool,
     uint16_t* __restrict__ vpool, int64_t rows, int32_t hkv, int32_t* __restrict__ node_len,
-    const AppendPiece* __restrict__ pieces, int32_t n, const int2* __restrict__ upd, int32_t n_upd) {
-  __shared__ uint16_t vt[kTile * (D + 2)];
-  if (node_len != nullptr && blockIdx.y == 0 && threadIdx.x == 0 && static_cast<int>(blockIdx.x) < n_upd) {
-    const int2 u = upd[blockIdx.x];
-    node_len[u.x] = u.y;
+    const AppendPiece* __restrict__ pieces, const int2* __restrict__ upd, int32_t n_upd,
+    const u32x4* __restrict__ image, u32x4* __restrict__ tables, int32_t n16, int32_t n_copy) {
+  __shared__ __attribute__((aligned(16))) uint32_t vt[append_lds_dwords<D>()];
+  const int bx = blockIdx.x;
+  if (bx < n_copy) {
+    if (blockIdx.y != 0) return;
+    u32x4 v[kCopyPer];
+#pragma unroll
+    for (int j = 0; j < kCopyPer; ++j) {
+      const int i = (bx * kCopyPer + j) * kThreads + static_cast<int>(threadIdx.x);
+      if (i < n16) v[j] = image[i];
+    }
+    if (node_len != nullptr)
+      for (int i = bx * kThreads + static_cast<int>(threadIdx.x); i < n_upd; i += n_copy * kThreads) {
+        const int2 u = upd[i];
+        node_len[u.x] = u.y;
+      }
+#pragma unroll
+    for (int j = 0; j < kCopyPer; ++j) {
+      const int i = (bx * kCopyPer + j) * kThreads + static_cast<int>(threadIdx.x);
+      if (i < n16) tables[i] = v[j];
+    }
+    return;
   }
-  if (static_cast<int>(blockIdx.x) >= n) return;
-  const AppendPiece pc = pieces[blockIdx.x];
-  append_piece<D>(ksrc, vsrc, kpool, vpool, rows, hkv, pc, vt);
+  append_piece<D>(ksrc, vsrc, kpool, vpool, rows, hkv, blockIdx.y, pieces[bx - n_copy], vt);
 }
-
 
 // ---- prefill ------------------------------------------------------------------------
 //
@@ -1480,20 +1539,21 @@ hipError_t launch_prefill(const PrefillArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_kv_append_dev(const uint16_t* k_src, const uint16_t* v_src, uint16_t* k_pool, uint16_t* v_pool,
-                                int64_t rows, int32_t hkv, int32_t d, const AppendPiece* pieces,
-                                int32_t n_pieces, const int2* upd, int32_t n_upd, int32_t* node_len,
-                                hipStream_t s) {
-  if (node_len == nullptr) n_upd = 0;
-  const int32_t gx = n_pieces > n_upd ? n_pieces : n_upd;
-  if (gx <= 0) return hipSuccess;
-  const dim3 grid(static_cast<unsigned>(gx), static_cast<unsigned>(hkv));
-  if (d == 128)
-    kv_append_dev_kernel<128><<<grid, kThreads, 0, s>>>(k_src, v_src, k_pool, v_pool, rows, hkv, node_len,
-                                                       pieces, n_pieces, upd, n_upd);
+hipError_t launch_prefill_append(const PrefillAppendArgs& a, hipStream_t s) {
+  if (a.n_pieces <= 0 || a.table_bytes == 0 || a.table_bytes % 16 != 0) return hipErrorInvalidValue;
+  const int32_t n16 = static_cast<int32_t>(a.table_bytes / 16);
+  const int32_t n_copy = (n16 + kThreads * kCopyPer - 1) / (kThreads * kCopyPer);
+  const dim3 grid(static_cast<unsigned>(n_copy + a.n_pieces), static_cast<unsigned>(a.hkv));
+  const auto* image = static_cast<const u32x4*>(a.image);
+  auto* tables = static_cast<u32x4*>(a.tables);
+  if (a.d == 128)
+    prefill_append_kernel<128><<<grid, kThreads, 0, s>>>(a.k_src, a.v_src, a.k_pool, a.v_pool, a.pool_rows, a.hkv,
+                                                         a.node_len, a.pieces, a.upd, a.n_upd, image, tables, n16,
+                                                         n_copy);
   else
-    kv_append_dev_kernel<64><<<grid, kThreads, 0, s>>>(k_src, v_src, k_pool, v_pool, rows, hkv, node_len,
-                                                      pieces, n_pieces, upd, n_upd);
+    prefill_append_kernel<64><<<grid, kThreads, 0, s>>>(a.k_src, a.v_src, a.k_pool, a.v_pool, a.pool_rows, a.hkv,
+                                                        a.node_len, a.pieces, a.upd, a.n_upd, image, tables, n16,
+                                                        n_copy);
   return hipGetLastError();
 }
 

@@ -1034,24 +1034,36 @@ int32_t treepo_prefill(treepo_ctx* ctx, int32_t n, const int32_t* nodes, const i
     return fail(ctx, TREEPO_EWORKSPACE,
                 "workspace missing, smaller than treepo_prefill_workspace_size or not 256-byte aligned");
   char* wsb = static_cast<char*>(workspace);
-  std::vector<char> blob(pl.bytes, 0);
-  std::memcpy(blob.data(), pl.items.data(), pl.items.size() * sizeof(treepo::PrefillItem));
-  std::memcpy(blob.data() + pl.tiles_off, pl.tiles.data(), pl.tiles.size() * sizeof(int32_t));
-  std::memcpy(blob.data() + pl.sched_off, pl.sched.data(), pl.sched.size() * sizeof(int32_t));
-  std::memcpy(blob.data() + pl.pieces_off, pl.pieces.data(), pl.pieces.size() * sizeof(treepo::AppendPiece));
-  std::memcpy(blob.data() + pl.upd_off, pl.upd.data(), pl.upd.size() * sizeof(int32_t));
-  hipError_t e = upload(ctx, wsb, blob.data(), blob.size(), stream);
-  if (e != hipSuccess) return hip_fail(ctx, e, "prefill table upload");
-  // the append: every piece in one launch, from the uploaded tables
-  e = timed_launch(ctx, TREEPO_KERNEL_APPEND, stream, [&] {
-    return treepo::launch_kv_append_dev(
-        static_cast<const uint16_t*>(k), static_cast<const uint16_t*>(v), static_cast<uint16_t*>(ctx->cfg.k_pool),
-        static_cast<uint16_t*>(ctx->cfg.v_pool), pool_rows(ctx), ctx->cfg.num_kv_heads, ctx->cfg.head_dim,
-        reinterpret_cast<const treepo::AppendPiece*>(wsb + pl.pieces_off), static_cast<int32_t>(pl.pieces.size()),
-        reinterpret_cast<const int2*>(wsb + pl.upd_off), static_cast<int32_t>(pl.upd.size() / 2),
-        static_cast<int32_t*>(ctx->cfg.node_len), stream);
-  });
+  PinnedSlot* sl = nullptr;
+  hipError_t e = acquire_slot(ctx, pl.bytes, &sl);
+  if (e != hipSuccess) return hip_fail(ctx, e, "prefill table staging");
+  char* img = static_cast<char*>(sl->p);
+  std::memcpy(img, pl.items.data(), pl.items.size() * sizeof(treepo::PrefillItem));
+  std::memcpy(img + pl.tiles_off, pl.tiles.data(), pl.tiles.size() * sizeof(int32_t));
+  std::memcpy(img + pl.sched_off, pl.sched.data(), pl.sched.size() * sizeof(int32_t));
+  std::memcpy(img + pl.pieces_off, pl.pieces.data(), pl.pieces.size() * sizeof(treepo::AppendPiece));
+  if (!pl.upd.empty()) std::memcpy(img + pl.upd_off, pl.upd.data(), pl.upd.size() * sizeof(int32_t));
+  // the append: every piece in one launch, which also moves the tables to the workspace
+  treepo::PrefillAppendArgs pa;
+  pa.k_src = static_cast<const uint16_t*>(k);
+  pa.v_src = static_cast<const uint16_t*>(v);
+  pa.k_pool = static_cast<uint16_t*>(ctx->cfg.k_pool);
+  pa.v_pool = static_cast<uint16_t*>(ctx->cfg.v_pool);
+  pa.pool_rows = pool_rows(ctx);
+  pa.hkv = ctx->cfg.num_kv_heads;
+  pa.d = ctx->cfg.head_dim;
+  pa.node_len = static_cast<int32_t*>(ctx->cfg.node_len);
+  pa.pieces = reinterpret_cast<const treepo::AppendPiece*>(img + pl.pieces_off);
+  pa.n_pieces = static_cast<int32_t>(pl.pieces.size());
+  pa.upd = reinterpret_cast<const int2*>(img + pl.upd_off);
+  pa.n_upd = static_cast<int32_t>(pl.upd.size() / 2);
+  pa.image = img;
+  pa.tables = wsb;
+  pa.table_bytes = pl.pieces_off;
+  e = timed_launch(ctx, TREEPO_KERNEL_APPEND, stream, [&] { return treepo::launch_prefill_append(pa, stream); });
+  const hipError_t rel = release_slot(sl, stream);
   if (e != hipSuccess) return hip_fail(ctx, e, "prefill append launch");
+  if (rel != hipSuccess) return hip_fail(ctx, rel, "prefill table staging");
   ctx->tree.apply_append(n, nodes, ntok);
   treepo::PrefillArgs a;
   a.k_pool = static_cast<const uint16_t*>(ctx->cfg.k_pool);
