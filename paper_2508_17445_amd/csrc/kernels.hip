@@ -998,7 +998,7 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(const int2* __restric
 // piece covers the 8 tokens in part, the 2-byte entries that it holds.  Bound
 // by memory: the rows of 64 prompts of 256-1024 tokens (4 KV heads of D 128,
 // 169 MB read and written) took 45 us with 2-byte stores and one row chunk in
-// flight per thread, kMeasuredBatch us now.
+// flight per thread, 35 us now.
 constexpr int kMaxPieces = 128;
 struct AppendBatch {
   int32_t n;      // pieces
@@ -1085,6 +1085,47 @@ __global__ __launch_bounds__(kThreads) void kv_append_kernel(const uint16_t* __r
     node_len[b.upd[blockIdx.x].x] = b.upd[blockIdx.x].y;
   if (static_cast<int>(blockIdx.x) >= b.n) return;
   append_piece<D>(ksrc, vsrc, kpool, vpool, rows, hkv, blockIdx.y, b.p[blockIdx.x], vt);
+}
+
+// A step of segment decoding: one token per piece, row i of the source for
+// piece i.  Latency is all there is, so no LDS and no idle lanes: a thread
+// takes one dword of K or V of one (piece, KV head) -- consecutive lanes
+// consecutive dwords -- and stores it as it is or as two entries of the
+// transposed group (16 bytes a thread took 8 scattered stores each: 8.7 us).
+// 256 leaves (8 KV heads, D 128): two launches of one workgroup per (piece,
+// head), 12.8 us, against one of 8.1 us.
+constexpr int kMaxStepPieces = 256;
+struct StepBatch {
+  int32_t n, n_upd, src0;
+  int32_t block[kMaxStepPieces];  // 64-row chunk of the pool
+  uint8_t off[kMaxStepPieces];    // row in it
+  int2 upd[kMaxStepPieces];       // (node, length)
+};
+static_assert(sizeof(StepBatch) <= 3584, "fits the kernel arguments beside the pointers");
+
+template <int D>
+__global__ __launch_bounds__(kThreads) void kv_step_kernel(const uint16_t* __restrict__ ksrc,
+                                                           const uint16_t* __restrict__ vsrc,
+                                                           uint16_t* __restrict__ kpool,
+                                                           uint16_t* __restrict__ vpool, int64_t rows, int32_t hkv,
+                                                           int32_t* __restrict__ node_len, StepBatch b) {
+  constexpr int kCh = D / 2;
+  const int id = blockIdx.x * kThreads + threadIdx.x;
+  if (node_len != nullptr && id < b.n_upd) node_len[b.upd[id].x] = b.upd[id].y;
+  const int c = id % kCh, pair = id / kCh >> 1;
+  const bool is_v = (id / kCh & 1) != 0;
+  const int i = pair / hkv, g = pair - i * hkv;
+  if (i >= b.n) return;
+  const int64_t src = (static_cast<int64_t>(b.src0 + i) * hkv + g) * D + c * 2;
+  const uint32_t x = *reinterpret_cast<const uint32_t*>((is_v ? vsrc : ksrc) + src);
+  const int64_t row = static_cast<int64_t>(g) * rows + static_cast<int64_t>(b.block[i]) * kTile + b.off[i];
+  if (!is_v) {
+    *reinterpret_cast<uint32_t*>(kpool + row * D + c * 2) = x;
+  } else {
+    uint16_t* dst = vpool + (row / kVGroup) * kVGroup * D + c * 2 * kVGroup + row % kVGroup;
+    dst[0] = static_cast<uint16_t>(x);
+    dst[kVGroup] = static_cast<uint16_t>(x >> 16);
+  }
 }
 
 // The append of a prefill, and its tables.  The host writes one image (pinned
@@ -1562,6 +1603,32 @@ hipError_t launch_kv_append(const uint16_t* k_src, const uint16_t* v_src, uint16
                             const AppendPiece* pieces, int32_t n_pieces, const int32_t* upd_node,
                             const int32_t* upd_len, int32_t n_upd, int32_t* node_len, hipStream_t s) {
   if (node_len == nullptr) n_upd = 0;
+  bool step = n_pieces > 0;  // one token per piece: their source rows follow one another
+  for (int32_t i = 0; i < n_pieces; ++i) step = step && pieces[i].count == 1 && pieces[i].src_row == i;
+  if (step) {
+    // n_upd <= n_pieces, and the threads of one KV head's rows outnumber the pieces
+    for (int32_t p0 = 0; p0 < n_pieces; p0 += kMaxStepPieces) {
+      StepBatch b;
+      b.n = n_pieces - p0 < kMaxStepPieces ? n_pieces - p0 : kMaxStepPieces;
+      b.n_upd = n_upd - p0 < b.n ? (n_upd > p0 ? n_upd - p0 : 0) : b.n;
+      b.src0 = p0;
+      for (int32_t i = 0; i < b.n; ++i) {
+        b.block[i] = pieces[p0 + i].block;
+        b.off[i] = static_cast<uint8_t>(pieces[p0 + i].off);
+      }
+      for (int32_t i = 0; i < b.n_upd; ++i) b.upd[i] = make_int2(upd_node[p0 + i], upd_len[p0 + i]);
+      const int64_t threads = static_cast<int64_t>(b.n) * hkv * d;
+      if (threads > INT32_MAX) return hipErrorInvalidValue;
+      const dim3 grid(static_cast<unsigned>((threads + kThreads - 1) / kThreads));
+      if (d == 128)
+        kv_step_kernel<128><<<grid, kThreads, 0, s>>>(k_src, v_src, k_pool, v_pool, rows, hkv, node_len, b);
+      else
+        kv_step_kernel<64><<<grid, kThreads, 0, s>>>(k_src, v_src, k_pool, v_pool, rows, hkv, node_len, b);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
   for (int32_t p0 = 0; p0 < n_pieces || p0 < n_upd; p0 += kMaxPieces) {
     AppendBatch b{};
     b.n = n_pieces - p0 < kMaxPieces ? (n_pieces > p0 ? n_pieces - p0 : 0) : kMaxPieces;
