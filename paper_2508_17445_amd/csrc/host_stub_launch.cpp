@@ -8,6 +8,7 @@ namespace treepo {
 
 hipError_t launch_partial(const DecodeArgs&, hipStream_t) { return hipErrorNoDevice; }
 hipError_t launch_combine(const DecodeArgs&, hipStream_t) { return hipErrorNoDevice; }
+hipError_t launch_direct(const DecodeArgs&, hipStream_t) { return hipErrorNoDevice; }
 int32_t partial_workgroups_per_cu() { return 2; }
 hipError_t noalloc_scratch(void**, uint64_t**) { return hipErrorNoDevice; }
 hipError_t launch_advantage(const AdvantageArgs&, hipStream_t) { return hipErrorNoDevice; }

@@ -25,6 +25,8 @@ struct DecodeArgs {
   float* part_ml;          // fp32 [partial_rows][2]: running max (log2 units), sum
   const int2* comb;           // per key (leaf, KV head): {first entry, entries to merge}
   int32_t emax;               // entries per key at most (partial slot stride of strided plans)
+  const int4* direct;         // direct form: DirectTile records (tree_core.h), direct_stride per leaf
+  int32_t direct_stride;
   bool compact;               // entries packed by prefix sums (else key k starts at entry k * emax)
   // Profiling: when set, the launch records these events at the kernel's
   // start and end (hipExtLaunchKernelGGL), so they time the kernel alone.
@@ -45,6 +47,8 @@ hipError_t noalloc_scratch(void** ptr, uint64_t** holder);
 // One workgroup per stream: every piece's node partials.
 hipError_t launch_partial(const DecodeArgs& a, hipStream_t s);
 hipError_t launch_combine(const DecodeArgs& a, hipStream_t s);
+// The whole decode of a small plan in one kernel: one workgroup per (leaf, KV head).
+hipError_t launch_direct(const DecodeArgs& a, hipStream_t s);
 // Node-partial workgroups resident per compute unit (set by the kernel's
 // register and LDS budget); the planner makes one stream per resident slot.
 int32_t partial_workgroups_per_cu();

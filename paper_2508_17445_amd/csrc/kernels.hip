@@ -989,6 +989,158 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(const int2* __restric
   if (lse != nullptr && lane == 0) lse[static_cast<int64_t>(x) * hq + h] = (run_m + __log2f(run_l)) * kLn2;
 }
 
+// ---- direct decode ------------------------------------------------------------
+//
+// Small plans: one workgroup per key (leaf x, KV head g) takes the leaf's
+// whole chain, so nothing is merged across workgroups and the call is one
+// launch.  Wave w takes tiles w, w + W, ... of the chain, its K and V operands
+// straight from the pools into registers, the next tile's loads in flight
+// while one is computed (a tile that several leaves share is read by each of
+// them: at these sizes it comes from the caches); the waves' rows then meet
+// in LDS.  Bound by latency: the records, the operands and the merge are
+// three memory round trips.
+template <int D, int W>
+__global__ __launch_bounds__(64 * W, 2) void direct_kernel(
+    const int4* __restrict__ recs, int32_t stride, const int32_t* __restrict__ node_len,
+    const uint16_t* __restrict__ kpool, const uint16_t* __restrict__ vpool, const uint16_t* __restrict__ q,
+    float* __restrict__ out, float* __restrict__ lse, int32_t rows16, int32_t hq, int32_t hkv, int32_t group,
+    float scale_log2) {
+  constexpr int kKS = D / 32, kDB = D / 16, kC = D / 4;
+  constexpr int kRow = D + 4;  // floats of an LDS row
+  __shared__ __attribute__((aligned(16))) float so[W][16][kRow];
+  __shared__ float2 sml[W][16];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int a = lane >> 4, r16 = lane & 15;
+  const int x = blockIdx.x / hkv, g = blockIdx.x - x * hkv;
+  const int4* __restrict__ rl = recs + static_cast<int64_t>(x) * stride;
+  const uint16_t* __restrict__ kh = kpool + static_cast<int64_t>(g) * rows16 * kVGroup * D;
+  const uint16_t* __restrict__ vh = vpool + static_cast<int64_t>(g) * rows16 * kVGroup * D;
+  const int64_t row0 = static_cast<int64_t>(x) * hq + g * group;  // query and output row of h' = 0
+
+  // this lane's element offsets in a tile: K rows tau(0 / 1, r16), chunk a;
+  // V^T row r16, tokens 8 a .. 8 a + 7
+  const int ko0 = tau(0, r16) * D + a * 8, ko1 = tau(1, r16) * D + a * 8;
+  const int vo = (a >> 1) * (D * kVGroup) + r16 * kVGroup + (a & 1) * 8;
+  struct Tile {
+    uint4 k[2 * kKS], v[kDB];
+    int valid;
+  };
+  auto load = [&](int j, Tile& t) {
+    const int4 r = rl[j];  // wave-uniform
+    t.valid = -1;
+    if (r.x < 0) return;
+    const int64_t off = static_cast<int64_t>(r.x) * kVGroup * D;
+#pragma unroll
+    for (int ks = 0; ks < kKS; ++ks) {
+      t.k[2 * ks] = *reinterpret_cast<const uint4*>(kh + off + ko0 + ks * 32);
+      t.k[2 * ks + 1] = *reinterpret_cast<const uint4*>(kh + off + ko1 + ks * 32);
+    }
+#pragma unroll
+    for (int db = 0; db < kDB; ++db) t.v[db] = *reinterpret_cast<const uint4*>(vh + off + vo + db * 16 * kVGroup);
+    t.valid = r.y;
+    if (r.z >= 0) {
+      const int n = node_len[r.z] - r.w;
+      t.valid = n < 0 ? 0 : (n > kSub ? kSub : n);
+    }
+  };
+
+  uint4 qb[kKS];
+#pragma unroll
+  for (int ks = 0; ks < kKS; ++ks)
+    qb[ks] = r16 < group ? *reinterpret_cast<const uint4*>(q + (row0 + r16) * D + (4 * ks + a) * 8)
+                         : make_uint4(0, 0, 0, 0);
+  f32x4 acc[kDB];
+#pragma unroll
+  for (int db = 0; db < kDB; ++db) acc[db] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m_ref = -INFINITY, l_sum = 0.f;
+
+  auto compute = [&](const Tile& t) {
+    if (t.valid <= 0) return;
+    f32x4 S[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int ks = 0; ks < kKS; ++ks) {
+      S[0] = mfma16(t.k[2 * ks], qb[ks], S[0]);
+      S[1] = mfma16(t.k[2 * ks + 1], qb[ks], S[1]);
+    }
+    float s[2][4];
+    float mx = -INFINITY;
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        s[b][e] = 8 * a + 4 * b + e < t.valid ? S[b][e] * scale_log2 : -INFINITY;
+        mx = fmaxf(mx, s[b][e]);
+      }
+    if (__builtin_amdgcn_ballot_w64(mx > m_ref + kLazyMaxSlack) != 0) {
+      mx = fmaxf(mx, __shfl_xor(mx, 16));
+      mx = fmaxf(mx, __shfl_xor(mx, 32));
+      const float mn = fmaxf(m_ref, mx);
+      const float alpha = m_ref == -INFINITY ? 0.f : fast_exp2(m_ref - mn);
+      m_ref = mn;
+      l_sum *= alpha;
+#pragma unroll
+      for (int db = 0; db < kDB; ++db) acc[db] *= alpha;
+    }
+    uint2 p0, pl0, p1, pl1;
+    l_sum += softmax_p4(s[0], m_ref, p0, pl0) + softmax_p4(s[1], m_ref, p1, pl1);
+    const uint4 P = make_uint4(p0.x, p0.y, p1.x, p1.y), PL = make_uint4(pl0.x, pl0.y, pl1.x, pl1.y);
+#pragma unroll
+    for (int db = 0; db < kDB; ++db) {
+      uint4 va = t.v[db];
+      if (t.valid < kSub) {
+        const uint2 lo = mask_v4(make_uint2(va.x, va.y), 8 * a, t.valid);
+        const uint2 hi = mask_v4(make_uint2(va.z, va.w), 8 * a + 4, t.valid);
+        va = make_uint4(lo.x, lo.y, hi.x, hi.y);
+      }
+      acc[db] = mfma16(va, PL, mfma16(va, P, acc[db]));
+    }
+  };
+  Tile t0, t1;
+  int j = wave;
+  if (j < stride) load(j, t0);
+  for (; j < stride; j += 2 * W) {
+    if (j + W < stride) load(j + W, t1);
+    compute(t0);
+    if (j + W >= stride) break;
+    if (j + 2 * W < stride) load(j + 2 * W, t0);
+    compute(t1);
+  }
+
+  // ---- the waves' rows: m* = max m, L = sum l 2^(m - m*), out = sum 2^(m - m*) O / L
+  l_sum += __shfl_xor(l_sum, 16);
+  l_sum += __shfl_xor(l_sum, 32);
+  if (r16 < group) {
+#pragma unroll
+    for (int db = 0; db < kDB; ++db) *reinterpret_cast<f32x4*>(&so[wave][r16][4 * (4 * db + a)]) = acc[db];
+    if (a == 0) sml[wave][r16] = make_float2(m_ref, l_sum);
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < group * kC; i += 64 * W) {
+    const int r = i / kC, c = i % kC;
+    float m[W], w[W];
+    float ms = -INFINITY, L = 0.f;
+#pragma unroll
+    for (int v = 0; v < W; ++v) {
+      const float2 ml = sml[v][r];
+      m[v] = ml.x;
+      w[v] = ml.y;
+      ms = fmaxf(ms, m[v]);
+    }
+    f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int v = 0; v < W; ++v) {
+      const float e = m[v] == -INFINITY ? 0.f : fast_exp2(m[v] - ms);
+      L += e * w[v];
+      const f32x4 ov = *reinterpret_cast<const f32x4*>(&so[v][r][4 * c]);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) o[k] = e == 0.f ? o[k] : fmaf(e, ov[k], o[k]);
+    }
+    *reinterpret_cast<f32x4*>(out + (row0 + r) * D + 4 * c) = o * (1.f / L);
+    if (lse != nullptr && c == 0) lse[row0 + r] = (ms + __log2f(L)) * kLn2;
+  }
+}
+
 // ---- KV append --------------------------------------------------------------
 //
 // One workgroup per (piece, KV head).  K rows are copied with 16-byte moves;
@@ -1557,6 +1709,20 @@ hipError_t launch_combine(const DecodeArgs& a, hipStream_t s) {
     launch_combine_d<128>(a, grid, s);
   else
     launch_combine_d<64>(a, grid, s);
+  return hipGetLastError();
+}
+
+hipError_t launch_direct(const DecodeArgs& a, hipStream_t s) {
+  constexpr int kW = 8;
+  if (a.direct_stride <= 0 || a.group > 16 || a.n_leaves <= 0) return hipErrorInvalidValue;
+  const dim3 grid(static_cast<unsigned>(a.n_leaves * a.hkv)), block(64 * kW);
+  const int32_t rows16 = static_cast<int32_t>(a.pool_rows / kVGroup);
+  if (a.d == 128)
+    launch_timed_block(a, direct_kernel<128, kW>, grid, block, s, a.direct, a.direct_stride, a.node_len, a.k_pool,
+                       a.v_pool, a.q, a.out, a.lse, rows16, a.hq, a.hkv, a.group, a.scale_log2);
+  else
+    launch_timed_block(a, direct_kernel<64, kW>, grid, block, s, a.direct, a.direct_stride, a.node_len, a.k_pool,
+                       a.v_pool, a.q, a.out, a.lse, rows16, a.hq, a.hkv, a.group, a.scale_log2);
   return hipGetLastError();
 }
 

@@ -698,4 +698,41 @@ int32_t build_plan(const Tree& t, int32_t n_leaves, const int32_t* leaves, PlanM
   return kOk;
 }
 
+void direct_table(const Tree& t, int32_t n_leaves, const int32_t* leaves, const PlanParams& p, Plan* out) {
+  constexpr int32_t T = kPlanTileTokens;
+  const auto& nd = t.nodes();
+  if (out->mode != kModeTree || p.group > kDirectMaxRows) return;
+  const int64_t keys = static_cast<int64_t>(n_leaves) * p.num_kv_heads;
+  if (keys > kDirectMaxKeys) return;
+  const int32_t max_tiles = static_cast<int32_t>((keys < kDirectFewKeys ? kDirectChainFew : kDirectChain) / p.head_dim);
+  auto grows = [&](const Node& x) { return p.live_lengths && x.n_children == 0 && x.len < x.cap; };
+  auto tiles = [&](const Node& x) { return ((grows(x) ? x.cap : x.len) + T - 1) / T; };
+  int64_t visits = 0;
+  int32_t stride = 0;
+  for (int32_t i = 0; i < n_leaves; ++i) {
+    int32_t n = 0;
+    for (int32_t y = leaves[i]; y != -1 && n <= max_tiles; y = nd[y].parent) n += tiles(nd[y]);
+    if (n > max_tiles) return;
+    visits += static_cast<int64_t>(n) * p.num_kv_heads;
+    stride = std::max(stride, n);
+  }
+  if (stride == 0 || visits * p.head_dim > kDirectVisits) return;
+  out->direct_stride = stride;
+  out->direct.assign(static_cast<size_t>(n_leaves) * stride, DirectTile{-1, 0, -1, 0});
+  std::vector<int32_t> ch;
+  for (int32_t i = 0; i < n_leaves; ++i) {
+    DirectTile* w = &out->direct[static_cast<size_t>(i) * stride];
+    t.chain(leaves[i], &ch);
+    for (int32_t y : ch) {
+      const Node& x = nd[y];
+      for (int32_t k = 0; k < tiles(x); ++k) {
+        const int64_t row = static_cast<int64_t>(x.block_begin) * t.block_tokens() + static_cast<int64_t>(k) * T;
+        const bool live = grows(x) && (k + 1) * T > x.len;
+        *w++ = DirectTile{static_cast<int32_t>(row / 16), std::max(0, std::min(T, x.len - k * T)), live ? y : -1,
+                          k * T};
+      }
+    }
+  }
+}
+
 }  // namespace treepo

@@ -110,6 +110,27 @@ enum PlanMode : int32_t { kModeTree = 0, kModeNaive = 1 };
 // exactly the rows each key holds.
 constexpr int64_t kStridedCombineBytes = int64_t{8} << 20;
 
+// Rule of the direct form (Plan::direct): its time is a floor of 4 us plus, per
+// round of 8 tiles of the longest chain, 1.05 us at D = 64 and 2.1 at 128
+// (more once the keys pass two per CU); the streams and their combine need two
+// launches, 10 us at the least, and grow with the KV bytes.  Measured, kernels
+// and the gap between them, streams / direct, D = 128 and 4 KV heads, three
+// quarters of every chain shared:
+//   keys   tiles: 5        20         40         64
+//     16   13.0 /  5.7  11.9 / 10.4 13.3 / 16.0 14.5 / 21.1
+//     64   14.5 /  5.6  15.4 / 10.6 18.2 / 16.3 20.4 / 21.8
+//    256   15.2 /  6.4  21.2 / 10.8 25.3 / 18.6 27.0 / 26.2
+//    512   20.3 / 10.1  25.1 / 20.0 31.3 / 33.9
+//   1024   22.6 / 16.9  32.1 / 37.9                          (8 KV heads)
+// and D = 64: 16 keys 40 tiles 10.7 / 9.5, 64 keys 64 tiles 15.2 / 12.9, 256
+// keys 64 tiles 21.8 / 15.1.  So the bounds, as tiles times D:
+constexpr int32_t kDirectMaxRows = 16;           // query rows of a key: one 16-row block
+constexpr int64_t kDirectMaxKeys = 1024;         // (leaf, KV head) pairs
+constexpr int64_t kDirectFewKeys = 64;           // below: the streams' workgroups are few and short too
+constexpr int64_t kDirectChainFew = 20 * 128;    // longest chain with few keys
+constexpr int64_t kDirectChain = 40 * 128;       // longest chain
+constexpr int64_t kDirectVisits = 10240 * 128;   // all keys' tiles
+
 // Tokens per decode tile (32 consecutive rows of a node from a 16-row line of the pool).
 constexpr int32_t kPlanTileTokens = 32;
 // Upper bounds on the tiles, query segments and pieces of one stream (sized
@@ -225,6 +246,16 @@ struct PlanParams {
   bool live_lengths;
 };
 
+// A tile of one leaf's chain: hb as in StreamTile, of KV head 0; `valid`
+// tokens, or, with node >= 0, those of node's current length past `base`.
+struct DirectTile {
+  int32_t hb;
+  int32_t valid;
+  int32_t node;  // live tile: its node; -1: `valid` holds
+  int32_t base;
+};
+static_assert(sizeof(DirectTile) == 16, "direct tile record size");
+
 struct Plan {
   PlanMode mode = kModeTree;
   std::vector<Stream> streams;
@@ -253,6 +284,12 @@ struct Plan {
   bool compact = false;
   std::vector<int32_t> dests;
   int64_t partial_rows = 0;
+  // Small plans (direct_table): the decode runs one workgroup per (leaf, KV
+  // head) over the leaf's whole chain and merges nothing across workgroups.
+  // Leaf x's tiles are DirectTile records [x * direct_stride, + direct_stride),
+  // chain order, the rest of the stride hb = -1.  0: the streams above run.
+  std::vector<DirectTile> direct;
+  int32_t direct_stride = 0;
   int64_t unique_kv_tokens = 0;   // tokens streamed per KV head (tree: unique)
   int64_t kv_token_visits = 0;    // tokens streamed, summed over leaf groups (per KV head)
 };
@@ -270,6 +307,10 @@ int32_t branch_budget(int32_t n, const float* scores, int32_t total, int32_t mod
 // Builds the decode schedule for `leaves` (validated by the caller).
 int32_t build_plan(const Tree& t, int32_t n_leaves, const int32_t* leaves, PlanMode mode,
                    const PlanParams& p, Plan* out, std::string* err);
+
+// Fills Plan::direct for a plan of these leaves where that is the faster
+// form (the rule is at its definition); else leaves direct_stride 0.
+void direct_table(const Tree& t, int32_t n_leaves, const int32_t* leaves, const PlanParams& p, Plan* out);
 
 // Node -> ascending call positions of the leaves whose chain contains it, for
 // every node on some chain (ascending id).

@@ -51,7 +51,7 @@ struct CachedPlan {
   std::vector<int32_t> leaves;
   Plan plan;
   std::vector<char> blob;  // host image of the plan's device data
-  size_t off_blocks = 0;
+  size_t off_blocks = 0;  // stream blocks, or (plan.direct_stride > 0) the direct tiles
   size_t off_comb = 0;
   size_t off_part_o = 0, off_part_ml = 0, ws_bytes = 0;  // partials, in the caller's workspace
   uint64_t last_use = 0;
@@ -396,22 +396,29 @@ int32_t get_plan(treepo_ctx* ctx, int32_t n, const int32_t* leaves, int32_t mode
   int32_t st = treepo::build_plan(ctx->tree, n, leaves, static_cast<PlanMode>(mode), ctx->params,
                                   &cp.plan, &err);
   if (st != treepo::kOk) return fail(ctx, st, err);
+  treepo::direct_table(ctx->tree, n, leaves, ctx->params, &cp.plan);
   const Plan& p = cp.plan;
   size_t off = 0;
   auto place = [&](size_t* at, size_t bytes) {
     *at = off;
     off = align_up(off + bytes);
   };
-  place(&cp.off_blocks, p.blocks.size() * sizeof(int32_t));
-  std::vector<int32_t> comb(2 * p.comb_count.size());
-  for (size_t k = 0; k < p.comb_count.size(); ++k) {
-    comb[2 * k] = p.comb_base[k];
-    comb[2 * k + 1] = p.comb_count[k];
+  if (p.direct_stride > 0) {
+    place(&cp.off_blocks, p.direct.size() * sizeof(treepo::DirectTile));
+    cp.blob.assign(off, 0);
+    put(cp.blob, cp.off_blocks, p.direct);
+  } else {
+    place(&cp.off_blocks, p.blocks.size() * sizeof(int32_t));
+    std::vector<int32_t> comb(2 * p.comb_count.size());
+    for (size_t k = 0; k < p.comb_count.size(); ++k) {
+      comb[2 * k] = p.comb_base[k];
+      comb[2 * k + 1] = p.comb_count[k];
+    }
+    place(&cp.off_comb, comb.size() * sizeof(int32_t));
+    cp.blob.assign(off, 0);
+    put(cp.blob, cp.off_blocks, p.blocks);
+    put(cp.blob, cp.off_comb, comb);
   }
-  place(&cp.off_comb, comb.size() * sizeof(int32_t));
-  cp.blob.assign(off, 0);
-  put(cp.blob, cp.off_blocks, p.blocks);
-  put(cp.blob, cp.off_comb, comb);
   off = 0;
   cp.off_part_o = off;
   // fp32 rows of D floats, or block floating-point rows of D / 2 dwords (compact plans)
@@ -492,15 +499,18 @@ int32_t launch_decode(treepo_ctx* ctx, const CachedPlan& cp, const char* img, ch
   a.comb = reinterpret_cast<const int2*>(img + cp.off_comb);
   a.emax = p.emax;
   a.compact = p.compact;
+  a.direct = reinterpret_cast<const int4*>(img + cp.off_blocks);
+  a.direct_stride = p.direct_stride;
   a.n_leaves = n;
   a.out = out;
   a.lse = lse;
   hipError_t e = timed_launch_attached(ctx, TREEPO_KERNEL_PARTIAL, [&](hipEvent_t t0, hipEvent_t t1) {
     a.ev_start = t0;
     a.ev_stop = t1;
-    return treepo::launch_partial(a, stream);
+    return p.direct_stride > 0 ? treepo::launch_direct(a, stream) : treepo::launch_partial(a, stream);
   });
   if (e != hipSuccess) return hip_fail(ctx, e, "partial kernel launch");
+  if (p.direct_stride > 0) return TREEPO_OK;
   e = timed_launch_attached(ctx, TREEPO_KERNEL_COMBINE, [&](hipEvent_t t0, hipEvent_t t1) {
     a.ev_start = t0;
     a.ev_stop = t1;

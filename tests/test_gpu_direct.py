@@ -1,0 +1,117 @@
+"""GPU parity of the one-kernel decode of small plans, at the edges of its rule
+and of its tiles, against the fp64 oracle and the per-leaf baseline (which
+always runs the streams).
+
+Tolerance: the weights carry two bf16 terms (relative error 2^-17), so an
+output moves by at most 2^-17 of the largest |V| it averages (below 5.5 for the
+N(0, 1) rows here: 4.2e-5), and fp32 accumulation adds less than 1e-6.
+"""
+
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from oracle import attention as A
+from tests.test_gpu_prefill import _Rig
+from workloads import node_kv_bits, query_bits
+
+TOL = 5e-5
+KERNEL_PARTIAL, KERNEL_COMBINE = 1, 2
+
+pytestmark = pytest.mark.gpu
+
+
+def _append(rig, nodes, ntok, step):
+    ks, vs = [], []
+    for x, t in zip(nodes, ntok):
+        k, v = node_kv_bits(rig.seed, 10_000 * step + x, t, rig.hkv, rig.d)
+        old = rig.kv.get(x)
+        rig.kv[x] = (k, v) if old is None else (np.concatenate([old[0], k]), np.concatenate([old[1], v]))
+        ks.append(k), vs.append(v)
+    rig.ctx.kv_append(nodes, ntok, rig.dev(np.concatenate(ks)), rig.dev(np.concatenate(vs)))
+    rig.model.append(nodes, ntok)
+
+
+def _grow(rig, parent, n, cap):
+    kids = [rig.ctx.new_root(cap)] if parent < 0 else rig.ctx.fork(parent, n, cap)
+    assert kids == ([rig.model.new_root(cap)] if parent < 0 else rig.model.fork(parent, n, cap))
+    for x in kids:
+        rig.kv.setdefault(x, node_kv_bits(rig.seed, x, 0, rig.hkv, rig.d))
+    return kids
+
+
+def _decode(rig, leaves, tag):
+    """Decodes in both modes; returns whether the tree decode was one kernel."""
+    import torch
+    q = query_bits(rig.seed, 77, len(leaves), rig.hq, rig.d)
+    ref, ref_l = A.tree_decode(rig.model, rig.node_kv, leaves, q, rig.scale)
+    qd = rig.dev(q)
+    rig.ctx.set_profiling(True)
+    merged = 0
+    for mode, fn in ((1, rig.ctx.paged_decode_naive), (0, rig.ctx.tree_decode)):
+        o = torch.full((len(leaves), rig.hq, rig.d), float("nan"), device="cuda")
+        l = torch.full((len(leaves), rig.hq), float("nan"), device="cuda")
+        ws = torch.empty(max(rig.ctx.workspace_size(leaves, mode), 256), dtype=torch.uint8, device="cuda")
+        merged = rig.ctx.profile_read(KERNEL_COMBINE)[1]
+        fn(leaves, qd, rig.scale, o, l, ws)
+        torch.cuda.synchronize()
+        err, err_l = float(np.abs(o.cpu().numpy() - ref).max()), float(np.abs(l.cpu().numpy() - ref_l).max())
+        print(f"[direct {tag} mode={mode}] max|out-oracle|={err:.3e} max|lse-oracle|={err_l:.3e}", flush=True)
+        assert err <= TOL and err_l <= TOL
+    direct = rig.ctx.profile_read(KERNEL_COMBINE)[1] == merged
+    rig.ctx.set_profiling(False)
+    return direct
+
+
+@pytest.mark.parametrize("live", [False, True])
+@pytest.mark.parametrize("hq,hkv,d,bt", [(4, 1, 64, 16), (16, 1, 128, 64), (17, 1, 64, 32), (8, 8, 128, 64),
+                                         (28, 4, 128, 16), (3, 3, 64, 64)])
+def test_ragged_chains(hq, hkv, d, bt, live):
+    """Nodes that end inside a tile, empty leaves, interior nodes and repeated leaves."""
+    print(f"[direct ragged hq={hq} hkv={hkv} d={d} B={bt} live={live}]", flush=True)
+    rig = _Rig(hq, hkv, d, 11 + hq, num_blocks=64 * 64 // bt, max_nodes=64, live=live, bt=bt)
+    (r,) = _grow(rig, -1, 1, 100)
+    _append(rig, [r], [33], 0)
+    assert _decode(rig, [r], "one root") == (hq // hkv <= 16)
+    a, b, c = _grow(rig, r, 3, 70)
+    _append(rig, [a, b], [1, 65], 1)
+    d1, d2 = _grow(rig, a, 2, 40)
+    _append(rig, [d1], [31], 2)
+    for leaves in ([d1, d2, b, c], [c], [r, a, d2, d2, b, r]):
+        assert _decode(rig, leaves, f"leaves {leaves}") == (hq // hkv <= 16)
+
+
+def test_live_steps():
+    """Lengths that grow on the device under one plan, over a tile's edge."""
+    print("[direct live steps]", flush=True)
+    rig = _Rig(14, 2, 128, 5, num_blocks=40, max_nodes=16, live=True, bt=16)
+    (r,) = _grow(rig, -1, 1, 50)
+    _append(rig, [r], [50], 0)
+    kids = _grow(rig, r, 3, 48)
+    for t in range(36):
+        _append(rig, kids[:2] if t % 2 else kids, [1] * (2 if t % 2 else 3), 1 + t)
+        if t % 5 == 0 or t > 28:
+            assert _decode(rig, kids, f"step {t}")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("keys,tiles,want", [(1, 20, True), (1, 21, False), (62, 20, True), (62, 21, False),
+                                             (64, 40, True), (64, 41, False), (256, 40, True), (258, 40, False),
+                                             (1024, 10, True), (1024, 11, False), (1026, 2, False)])
+def test_rule(keys, tiles, want, d):
+    """Both sides of each bound (tile counts for D = 128, twice as many at 64)."""
+    print(f"[direct rule keys={keys} tiles={tiles} d={d}]", flush=True)
+    hkv = 1 if keys == 1 else 2
+    n = keys // hkv
+    top = tiles * (128 // d)
+    if (keys, tiles) in ((1, 21), (62, 21), (64, 41)):
+        top = (tiles - 1) * (128 // d) + 1
+    rig = _Rig(2 * hkv, hkv, d, 3, num_blocks=top // 2 + n + 4, max_nodes=n + 1)
+    (r,) = _grow(rig, -1, 1, 32 * top)
+    _append(rig, [r], [32 * (top - 1) + (1 if n == 1 else 0)], 0)
+    leaves = [r]
+    if n > 1:
+        leaves = _grow(rig, r, n, 32)
+        _append(rig, leaves, [1 + i % 32 for i in range(n)], 1)
+    assert _decode(rig, leaves, f"keys={keys} tiles={top}") == want
