@@ -9,7 +9,7 @@ namespace treepo {
 hipError_t launch_partial(const DecodeArgs&, hipStream_t) { return hipErrorNoDevice; }
 hipError_t launch_combine(const DecodeArgs&, hipStream_t) { return hipErrorNoDevice; }
 hipError_t launch_direct(const DecodeArgs&, hipStream_t) { return hipErrorNoDevice; }
-int32_t partial_workgroups_per_cu() { return 2; }
+int32_t partial_workgroups_per_cu(int32_t d) { return d == 64 ? 3 : 2; }
 hipError_t noalloc_scratch(void**, uint64_t**) { return hipErrorNoDevice; }
 hipError_t launch_advantage(const AdvantageArgs&, hipStream_t) { return hipErrorNoDevice; }
 hipError_t launch_prefill(const PrefillArgs&, hipStream_t) { return hipErrorNoDevice; }

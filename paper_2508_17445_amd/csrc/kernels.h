@@ -51,7 +51,7 @@ hipError_t launch_combine(const DecodeArgs& a, hipStream_t s);
 hipError_t launch_direct(const DecodeArgs& a, hipStream_t s);
 // Node-partial workgroups resident per compute unit (set by the kernel's
 // register and LDS budget); the planner makes one stream per resident slot.
-int32_t partial_workgroups_per_cu();
+int32_t partial_workgroups_per_cu(int32_t d);
 
 // TreePO advantage (advantage.hip): one workgroup over an image built on the
 // host from the leaves' chains.  The call positions are ordered depth first

@@ -64,7 +64,14 @@ __device__ __forceinline__ uint32_t lds_addr(const void* p) {
 constexpr int kSub = 32;   // tokens per tile
 constexpr int kNBuf = 4;   // LDS tile buffers per workgroup
 constexpr int kDepth = 3;  // tiles in flight while one is consumed
-constexpr int kWgsPerCu = 2;
+// Workgroups per CU.  Two hide a D = 128 tile's chain of barrier, scores and
+// weights under its 16 KiB of loads; a D = 64 tile has half the bytes for the
+// same chain, and its buffers (32 KiB a workgroup) leave room for a third:
+// whole call of four 16-leaf trees 40.6 -> 38.2 us.  (Eight buffers and two
+// workgroups, one tree: 15.8 -> 17.9 us.)  The planner decides which plans use
+// the third.
+template <int D>
+constexpr int wgs_per_cu() { return D == 64 ? 3 : 2; }
 constexpr int kPrefillWaves = 4;  // waves per prefill workgroup (32 query rows each)
 
 template <int D>
@@ -705,7 +712,7 @@ __device__ __forceinline__ void rows_piece(TREEPO_PARTIAL_PARAMS, const PieceRec
 // pipeline: every load is a global->LDS load counted by hand and every piece
 // record comes from LDS, so no compiler-inserted wait ever drains it.
 template <int D>
-__global__ __launch_bounds__(kThreads, kWgsPerCu) void partial_kernel(const int32_t* __restrict__ blocks,
+__global__ __launch_bounds__(kThreads, wgs_per_cu<D>()) void partial_kernel(const int32_t* __restrict__ blocks,
                                                                      int32_t block_ints,
                                                                      const int32_t* __restrict__ node_len,
                                                                      TREEPO_PARTIAL_PARAMS) {
@@ -1655,7 +1662,7 @@ __global__ __launch_bounds__(64 * W, 2) void prefill_kernel(
 
 }  // namespace
 
-int32_t partial_workgroups_per_cu() { return kWgsPerCu; }
+int32_t partial_workgroups_per_cu(int32_t d) { return d == 64 ? wgs_per_cu<64>() : wgs_per_cu<128>(); }
 
 // Launches `kernel` on `s`; with a.ev_start set, the events record the
 // kernel's own start and end.

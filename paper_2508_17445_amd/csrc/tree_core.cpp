@@ -334,6 +334,12 @@ constexpr double kGuide = 2.0;
 constexpr double kSnapFinish = 1.0;
 constexpr double kSnapEarly = 0.5;
 constexpr double kGuideMinCost = 8.0;
+// Where a CU holds three workgroups (D = 64), a plan uses the third from this
+// cost per two-workgroup stream on; shorter streams pay more for the extra
+// starts than the third hides.  Whole call at D = 64, two / three, us: 16-leaf
+// tree of 14 tiles a stream 16.4 / 17.5, 22 tiles 21.5 / 22.4, 27 tiles 24.4 /
+// 23.8, 41 tiles 32.2 / 30.9, 55 tiles 40.6 / 38.2, 110 tiles 74.8 / 71.3.
+constexpr double kThirdSlotCost = 24.0;
 // A live tile empty at planning time costs a few loads and no compute until it
 // fills; the plan serves a whole segment, so it is weighted at about its
 // average over the segment.
@@ -468,7 +474,7 @@ int32_t build_plan(const Tree& t, int32_t n_leaves, const int32_t* leaves, PlanM
   // of an even share of the remainder, scaled by its die's speed, between
   // kGuideMinCost and a full LDS table), so the last streams to start are
   // short and the slots drain together.
-  const int64_t S0 = std::max(1, p.concurrent_wgs);
+  const int64_t S0 = std::max(1, total_cost >= kThirdSlotCost * p.guided_wgs ? p.concurrent_wgs : p.guided_wgs);
   const int32_t nx = p.xcds >= 1 && p.xcds <= 8 ? p.xcds : 1;
   auto xcd_speed = [&](int64_t s) { return nx > 1 ? p.xcd_speed[s % nx] : 1.0; };
   double xcd_mean = 0.0;
@@ -487,7 +493,7 @@ int32_t build_plan(const Tree& t, int32_t n_leaves, const int32_t* leaves, PlanM
     quota.resize(static_cast<size_t>(planned));
     std::vector<double> w(static_cast<size_t>(planned), 1.0);
     if (p.compute_units > 0)
-      for (int64_t s = 0; s < planned; ++s) w[s] = p.slot_speed[s < p.compute_units ? 0 : 1];
+      for (int64_t s = 0; s < planned; ++s) w[s] = p.slot_speed[std::min<int64_t>(2, s / p.compute_units)];
     for (int64_t s = 0; s < planned; ++s) w[s] *= xcd_speed(s);
     double wsum = 0.0;
     for (double x : w) wsum += x;
@@ -504,7 +510,7 @@ int32_t build_plan(const Tree& t, int32_t n_leaves, const int32_t* leaves, PlanM
   for (const Seq& sq : seqs) total_kv_cost += tile_cost(sq.n_leaves * G) * runs[sq.run].weight;
   auto guided_quota = [&](double acc_now) {
     const double speed = xcd_speed(static_cast<int64_t>(out->streams.size()) - 1) / xcd_mean;  // the open stream
-    const double share = speed * (total_kv_cost - kv_acc) / (kGuide * static_cast<double>(S0));
+    const double share = speed * (total_kv_cost - kv_acc) / (kGuide * static_cast<double>(std::max(1, p.guided_wgs)));
     return acc_now + std::min(full_stream, std::max(kGuideMinCost, share));
   };
   double acc = 0.0;

@@ -229,13 +229,17 @@ struct PlanParams {
   int32_t head_dim;         // D
   int64_t num_blocks;       // pool blocks per KV head
   int32_t max_rows;         // query rows of a piece at most (leaf groups are split to fit)
-  int32_t concurrent_wgs;   // workgroups resident at once (streams per round)
+  int32_t concurrent_wgs;   // workgroups resident at once (streams of a one-round plan)
+  // Divisor of the stream sizes of plans of several rounds: two per compute
+  // unit.  Three at D = 64 (what is resident) only adds cuts: partial kernel of
+  // the 64-prompt batch at D = 64 365 us with two, 371 with three.
+  int32_t guided_wgs;
   // Relative speed of a first-round stream by its slot on the CU.  The
   // dispatcher fills every CU's first slot before any second one, so stream s
   // runs in slot s / compute_units; streams are sized in proportion to
-  // slot_speed[slot] (both 1.0: equal cost per stream).
+  // slot_speed[slot] (all 1.0: equal cost per stream).
   int32_t compute_units;
-  double slot_speed[2];
+  double slot_speed[3];
   // Relative speed by accelerator die (XCD): workgroups are dealt to the
   // xcds dies round robin, so stream s runs on die s % xcds; stream sizes
   // (every round) are scaled by xcd_speed[s % xcds] (all 1.0: no scaling).

@@ -38,6 +38,10 @@ constexpr int32_t kComputeUnitsPerXcd = 32;
 // 0.93-0.94 as many tiles per microsecond as the even ones on every box
 // measured.  Streams are sized in proportion to these speeds.
 constexpr double kSecondSlotSpeed = 0.80;
+// Third workgroup of a CU (D = 64 alone): partial kernel of four 16-leaf trees
+// at speeds 1 / 0.8 / x: x = 0.8 37.1 us, 0.7 35.5, 0.6 34.0, 0.5 34.3 (all 1:
+// 37.0).
+constexpr double kThirdSlotSpeed = 0.65;
 constexpr double kOddXcdSpeed = 0.935;
 
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
@@ -720,9 +724,11 @@ void build_adv_plan(const treepo::Tree& t, int32_t n, const int32_t* leaves, Adv
 void set_machine(treepo_ctx* ctx, int32_t compute_units, int32_t xcds) {
   PlanParams& p = ctx->params;
   p.compute_units = compute_units;
-  p.concurrent_wgs = compute_units * treepo::partial_workgroups_per_cu();
+  p.concurrent_wgs = compute_units * treepo::partial_workgroups_per_cu(ctx->cfg.head_dim);
+  p.guided_wgs = 2 * compute_units;
   p.slot_speed[0] = 1.0;
   p.slot_speed[1] = kSecondSlotSpeed;
+  p.slot_speed[2] = kThirdSlotSpeed;
   p.xcds = xcds;
   for (int x = 0; x < 8; ++x) p.xcd_speed[x] = x % 2 ? kOddXcdSpeed : 1.0;
 }
