@@ -157,12 +157,19 @@ int32_t Tree::fork_at(int32_t node, int32_t offset, int32_t n, int32_t cap, int3
   return kOk;
 }
 
+bool strictly_ascending(int32_t n, const int32_t* x) {
+  for (int32_t i = 1; i < n; ++i)
+    if (x[i] <= x[i - 1]) return false;
+  return true;
+}
+
 int32_t Tree::check_append(int32_t n, const int32_t* nodes, const int32_t* ntok,
                            std::vector<int64_t>* dest_rows, std::string* err) const {
   if (n < 0 || (n > 0 && (!nodes || !ntok))) {
     if (err) *err = "bad append arrays";
     return kEInval;
   }
+  const bool once = strictly_ascending(n, nodes);  // no node twice: no lengths to carry
   std::unordered_map<int32_t, int32_t> pending;
   if (dest_rows) dest_rows->clear();
   for (int32_t i = 0; i < n; ++i) {
@@ -176,8 +183,11 @@ int32_t Tree::check_append(int32_t n, const int32_t* nodes, const int32_t* ntok,
       if (err) *err = "append to a node that has children";
       return kEFrozen;
     }
-    auto it = pending.find(nd);
-    const int32_t cur = it == pending.end() ? node.len : it->second;
+    int32_t cur = node.len;
+    if (!once) {
+      auto it = pending.find(nd);
+      if (it != pending.end()) cur = it->second;
+    }
     if (static_cast<int64_t>(cur) + ntok[i] > node.cap) {
       if (err) *err = "append past the node's capacity";
       return kEFull;
@@ -186,7 +196,7 @@ int32_t Tree::check_append(int32_t n, const int32_t* nodes, const int32_t* ntok,
       const int64_t base = static_cast<int64_t>(node.block_begin) * B_ + cur;
       for (int32_t k = 0; k < ntok[i]; ++k) dest_rows->push_back(base + k);
     }
-    pending[nd] = cur + ntok[i];
+    if (!once) pending[nd] = cur + ntok[i];
   }
   return kOk;
 }

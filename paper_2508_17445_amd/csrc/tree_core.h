@@ -38,6 +38,8 @@ struct Node {
   int32_t n_children;
 };
 
+bool strictly_ascending(int32_t n, const int32_t* x);
+
 class Tree {
  public:
   // With 16-token blocks the pool's last block is never reserved: a node's

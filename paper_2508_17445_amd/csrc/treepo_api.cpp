@@ -584,12 +584,16 @@ void append_pieces(const treepo::Tree& t, int32_t n, const int32_t* nodes, const
                    std::vector<std::pair<int32_t, int32_t>>* upd = nullptr) {
   const int32_t B = t.block_tokens();
   std::vector<std::pair<int32_t, int32_t>> pending;  // node -> len so far in this call
+  pending.reserve(n);
+  const bool once = treepo::strictly_ascending(n, nodes);  // no node twice: nothing to look up
   out->clear();
   int32_t src = 0;
   for (int32_t i = 0; i < n; ++i) {
     const treepo::Node& nd = t.nodes()[nodes[i]];
-    auto it = std::find_if(pending.begin(), pending.end(),
-                           [&](const std::pair<int32_t, int32_t>& pr) { return pr.first == nodes[i]; });
+    auto it = once ? pending.end()
+                   : std::find_if(pending.begin(), pending.end(), [&](const std::pair<int32_t, int32_t>& pr) {
+                       return pr.first == nodes[i];
+                     });
     int32_t cur = it == pending.end() ? nd.len : it->second;
     int32_t left = ntok[i];
     while (left > 0) {
