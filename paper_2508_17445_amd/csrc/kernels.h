@@ -110,6 +110,7 @@ struct PrefillArgs {
   float scale_log2;
   float* out;                // fp32 [rows][Hq][D]
   float* lse;                // fp32 [rows][Hq] or null
+  bool teams = false;        // two teams of waves per workgroup
   hipEvent_t ev_start = nullptr, ev_stop = nullptr;
 };
 hipError_t launch_prefill(const PrefillArgs& a, hipStream_t s);

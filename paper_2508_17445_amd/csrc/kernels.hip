@@ -1388,29 +1388,37 @@ __device__ __forceinline__ void dma16c(const void* sbase, uint32_t voff, uint32_
 constexpr int kPfAhead = 1;
 constexpr int kPfStages = kPfAhead + 1;  // LDS buffers of each of K and V
 
-template <int D, int W>
-__global__ __launch_bounds__(64 * W, 2) void prefill_kernel(
-    const uint16_t* __restrict__ kpool, const uint16_t* __restrict__ vpool, const uint16_t* __restrict__ q,
-    const PrefillItem* __restrict__ items, const int2* __restrict__ tiles, const int32_t* __restrict__ sched,
-    float* __restrict__ out, float* __restrict__ lse, int32_t n_sched, int32_t rows16, int32_t hq, int32_t hkv,
-    float scale_log2) {
+// Calls with few workgroups: half-size workgroups (W = 2 waves, 64 rows) of
+// NT = 2 teams that take the tiles in turn (team t tiles t, t + 2, ...), each
+// with its own buffers; the second team's rows join the first's in LDS at the
+// end.  A wave's chain of scores, weights and products takes about 0.73 us a
+// tile however idle the chip is; this halves the chain and gives each half a
+// SIMD of its own on the CUs that the large workgroups would leave empty.
+#define TREEPO_PREFILL_PARAMS                                                                                       \
+  const uint16_t *__restrict__ kpool, const uint16_t *__restrict__ vpool, const uint16_t *__restrict__ q,          \
+      const PrefillItem *__restrict__ items, const int2 *__restrict__ tiles, const int32_t *__restrict__ sched,    \
+      float *__restrict__ out, float *__restrict__ lse, int32_t n_sched, int32_t rows16, int32_t hq, int32_t hkv,  \
+      float scale_log2
+template <int D, int W, int NT>
+__device__ __forceinline__ void prefill_body(TREEPO_PREFILL_PARAMS) {
   constexpr int kKS = D / 16;                       // QK k-steps
   constexpr int kDB = D / 32;                       // PV output d-blocks
   constexpr int kHalf = kSub * D * 2;               // bytes of a K (or V^T) tile
   constexpr int kPer = kHalf / 1024 / W;            // 1 KiB slots per wave for each of K and V
   constexpr int kKChunks = D / 8;
   constexpr int kQBytes = 32 * D * 2;               // a wave's query rows
-  // K stages, V stages, every wave's query rows; at the end, its output rows
-  __shared__ __attribute__((aligned(1024))) char smem[2 * kPfStages * kHalf + W * kQBytes];
-  static_assert(sizeof(smem) >= W * 2 * kQBytes, "output rows fit");
-  char* const kbuf = smem;
-  char* const vbuf = smem + kPfStages * kHalf;
-  char* const qbuf = smem + 2 * kPfStages * kHalf;
+  constexpr int kTeam = 2 * kPfStages * kHalf;      // a team's K stages and V stages
+  // the teams' stages, every wave's query rows; at the end, the second team's
+  // rows and their (m, l), and the output rows
+  __shared__ __attribute__((aligned(1024))) char smem[NT * kTeam + W * kQBytes];
+  static_assert(sizeof(smem) >= W * 2 * kQBytes + (NT - 1) * W * 64 * 8, "output rows fit");
 
   const int G = hq / hkv;
   const int wg = blockIdx.x;
   const int s_x = wg >> 3;
-  const int slot = (s_x / G) * 8 + (wg & 7);
+  constexpr int kRows = 32 * W;                     // rows of a workgroup
+  constexpr int kSubs = kPrefillRows / kRows;       // workgroups of an item
+  const int slot = (s_x / (G * kSubs)) * 8 + (wg & 7);
   if (slot >= n_sched) return;  // whole workgroup
   int zero = 0;
   asm volatile("" : "+v"(zero));  // a vector load, beside the scalar loads of the arguments
@@ -1418,20 +1426,43 @@ __global__ __launch_bounds__(64 * W, 2) void prefill_kernel(
   if (unit < 0) return;
   const int item_i = unit / hkv;
   const int g = unit - item_i * hkv;
-  const int h = g * G + s_x % G;
+  const int h = g * G + (s_x / kSubs) % G;
+  const int row_off = (s_x % kSubs) * kRows;
 
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave_i = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int team = NT == 1 ? 0 : wave_i / W;
+  const int wave = wave_i - team * W;
+  char* const kbuf = smem + team * kTeam;
+  char* const vbuf = kbuf + kPfStages * kHalf;
+  char* const qbuf = smem + NT * kTeam;
   const int half = lane >> 5;
   const int r32 = lane & 31;
-  const PrefillItem it = items[item_i];
-  const int nk = it.nk;
+  PrefillItem it = items[item_i];
+  int nk_all = it.nk;
+  if constexpr (kSubs > 1) {
+    if (row_off >= it.n_rows) return;  // whole workgroup
+    // the item's last tiles, 32 tokens apart, start past the rows of an earlier part
+    const int last = it.pos0 + row_off + kRows - 1;
+    const int first = tiles[it.tile_off + nk_all - 1].y >> 6;
+    if (first > last) nk_all -= (first - last + kSub - 1) / kSub;
+    it.row0 += row_off;
+    it.pos0 += row_off;
+    it.n_rows = it.n_rows - row_off < kRows ? it.n_rows - row_off : kRows;
+  }
+  const int steps = (nk_all + NT - 1) / NT;            // of every team
+  const int nk = (nk_all - team + NT - 1) / NT;        // tiles of this team: steps or one less
   const int2* __restrict__ tl = tiles + it.tile_off;
+  // record of step t of team m; past the item's last tile, that tile's
+  auto record = [&](int t, int m) {
+    const int i = NT * t + m;
+    return tl[i < nk_all ? i : nk_all - 1];
+  };
   const int hb_base = g * rows16;  // KV head g's pool rows start at row 16 hb_base
 
   // The wave's query rows into its share of the LDS (rows past the item's
   // last repeat it), chunk c of row r at c ^ (r & 15) (r & 7 at D = 64).
-  {
+  if (team == 0) {
     constexpr int kQCh = D / 8;
     const uint16_t* qp = q + (static_cast<int64_t>(it.row0) * hq + h) * D;
 #pragma unroll
@@ -1478,10 +1509,15 @@ __global__ __launch_bounds__(64 * W, 2) void prefill_kernel(
   // records of tiles k .. k + kPfAhead + 1
   int2 rec[kPfAhead + 2];
 #pragma unroll
-  for (int t = 0; t < kPfAhead + 2; ++t) rec[t] = tl[t < nk ? t : nk - 1];
+  for (int t = 0; t < kPfAhead + 2; ++t) rec[t] = record(t, team);
+  int other[2] = {kSub, kSub};  // tokens of the other team's tiles k and k + 1
+  if constexpr (NT == 2) {
+    other[0] = record(0, 1 - team).y & 63;
+    other[1] = record(1, 1 - team).y & 63;
+  }
   // Loads in order: K of tile 0, then groups t = {V of tile t, K of tile
   // t + 1}, kPfAhead groups ahead, each as many loads whatever t is.
-  issue_k(rec[0].x, 0, ~0u);
+  issue_k(rec[0].x, 0, 0 < nk ? ~0u : 0u);
 #pragma unroll
   for (int t = 0; t < kPfAhead; ++t) {
     issue_v(rec[t].x, t, t < nk ? ~0u : 0u);
@@ -1577,10 +1613,12 @@ __global__ __launch_bounds__(64 * W, 2) void prefill_kernel(
   auto begin = [&]() {
     barrier_tile_landed<2 * kPer * (kPfAhead - 1)>();
     const int cnt = rec[0].y & 63;
-    if (cnt < kSub) {
+    // (every team waits at the second barrier when one has a partial tile)
+    const bool partial = NT == 1 ? cnt < kSub : cnt < kSub || other[0] < kSub;
+    if (partial) {
       uint16_t* vt = reinterpret_cast<uint16_t*>(vbuf + (k & (kPfStages - 1)) * kHalf);
 #pragma unroll 1
-      for (int i = threadIdx.x; i < D * kSub; i += 64 * W) {
+      for (int i = threadIdx.x - team * 64 * W; i < D * kSub; i += 64 * W) {
         const int d = i / kSub, t = i % kSub;
         if (t >= cnt) vt[d * kSub + (((t >> 3) ^ v_swz(d)) << 3) + (t & 7)] = 0;
       }
@@ -1598,8 +1636,11 @@ __global__ __launch_bounds__(64 * W, 2) void prefill_kernel(
     ++k;
 #pragma unroll
     for (int t = 0; t < kPfAhead + 1; ++t) rec[t] = rec[t + 1];
-    const int n = k + kPfAhead + 1;
-    rec[kPfAhead + 1] = tl[n < nk ? n : nk - 1];
+    rec[kPfAhead + 1] = record(k + kPfAhead + 1, team);
+    if constexpr (NT == 2) {
+      other[0] = other[1];
+      other[1] = record(k + 1, 1 - team).y & 63;
+    }
   };
 
   barrier_tile_landed<2 * kPer * kPfAhead>();  // the query rows and K of tile 0
@@ -1607,9 +1648,10 @@ __global__ __launch_bounds__(64 * W, 2) void prefill_kernel(
 #pragma unroll
   for (int ks = 0; ks < kKS; ++ks)
     qb[ks] = reinterpret_cast<const uint4*>(qbuf + wave * kQBytes)[r32 * kKChunks + ((2 * ks + half) ^ (r32 & (kKChunks - 1)))];
-  bool vis = wave_on;  // tile k holds keys of the wave's rows (tile 0 does)
+  // tile k holds keys of the wave's rows (the item's tile 0 does)
+  bool vis = wave_on && (NT == 1 || (nk > 0 && (rec[0].y >> 6) <= pos_hi));
   if (vis) weights(qk(0), rec[0].y);
-  for (; k < nk; advance()) {
+  for (; k < steps; advance()) {
     begin();
     if (!vis) {
       next_v();
@@ -1630,6 +1672,38 @@ __global__ __launch_bounds__(64 * W, 2) void prefill_kernel(
     if (vis) weights(S, rec[1].y);
   }
   barrier_tile_landed<0>();  // no load into this workgroup's LDS is left, and no wave reads a tile any more
+
+  // ---- the second team's rows, lane for lane
+  if constexpr (NT == 2) {
+    f32x4* xo = reinterpret_cast<f32x4*>(smem) + wave * kDB * 4 * 64 + lane;
+    float2* xml = reinterpret_cast<float2*>(smem + W * 2 * kQBytes) + wave * 64 + lane;
+    if (team == 1 && wave_on) {
+#pragma unroll
+      for (int db = 0; db < kDB; ++db)
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          xo[(db * 4 + c) * 64] = f32x4{acc[db][4 * c], acc[db][4 * c + 1], acc[db][4 * c + 2], acc[db][4 * c + 3]};
+      *xml = make_float2(m_ref, l_sum);
+    }
+    __syncthreads();
+    if (team == 1) return;
+    if (wave_on) {
+      const float2 o = *xml;
+      const float mn = fmaxf(m_ref, o.x);
+      const float a0 = m_ref == -INFINITY ? 0.f : fast_exp2(m_ref - mn);
+      const float a1 = o.x == -INFINITY ? 0.f : fast_exp2(o.x - mn);
+      m_ref = mn;
+      l_sum = l_sum * a0 + o.y * a1;
+#pragma unroll
+      for (int db = 0; db < kDB; ++db)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const f32x4 v = xo[(db * 4 + c) * 64];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[db][4 * c + e] = fmaf(acc[db][4 * c + e], a0, v[e] * a1);
+        }
+    }
+  }
 
   // ---- normalised rows and their log-sum-exp: through the wave's share of
   // the LDS, so that every store instruction writes whole rows (32 chunks of
@@ -1658,6 +1732,18 @@ __global__ __launch_bounds__(64 * W, 2) void prefill_kernel(
     if (lse != nullptr && half == 0 && r32 < n)
       lse[static_cast<int64_t>(it.row0 + row_w + r32) * hq + h] = (m_ref + __log2f(l)) * kLn2;
   }
+}
+
+#define TREEPO_PREFILL_ARGS kpool, vpool, q, items, tiles, sched, out, lse, n_sched, rows16, hq, hkv, scale_log2
+
+template <int D, int W>
+__global__ __launch_bounds__(64 * W, 2) void prefill_kernel(TREEPO_PREFILL_PARAMS) {
+  prefill_body<D, W, 1>(TREEPO_PREFILL_ARGS);
+}
+
+template <int D>
+__global__ __launch_bounds__(256, 2) void prefill_teams_kernel(TREEPO_PREFILL_PARAMS) {
+  prefill_body<D, 2, 2>(TREEPO_PREFILL_ARGS);
 }
 
 }  // namespace
@@ -1738,18 +1824,16 @@ hipError_t launch_prefill(const PrefillArgs& a, hipStream_t s) {
   if (a.hkv <= 0 || a.hq % a.hkv != 0 || (a.d != 64 && a.d != 128)) return hipErrorInvalidValue;
   if (a.n_sched <= 0 || a.n_sched % 8 != 0) return hipErrorInvalidValue;
   const int64_t group = a.hq / a.hkv;
-  const int64_t wgs = static_cast<int64_t>(a.n_sched) * group;
+  const int64_t wgs = static_cast<int64_t>(a.n_sched) * group * (a.teams ? 2 : 1);
   if (wgs > 0x7FFFFFFF || a.pool_rows % kVGroup != 0 || a.hkv * (a.pool_rows / kVGroup) > 0x7FFFFFFF)
     return hipErrorInvalidValue;
   const dim3 grid(static_cast<unsigned>(wgs));
   const int32_t nb = static_cast<int32_t>(a.pool_rows / kVGroup);
-  const dim3 block(64 * kPrefillWaves);
-  if (a.d == 128)
-    launch_timed_block(a, prefill_kernel<128, kPrefillWaves>, grid, block, s, a.k_pool, a.v_pool, a.q, a.items,
-                       a.tiles, a.sched, a.out, a.lse, a.n_sched, nb, a.hq, a.hkv, a.scale_log2);
-  else
-    launch_timed_block(a, prefill_kernel<64, kPrefillWaves>, grid, block, s, a.k_pool, a.v_pool, a.q, a.items,
-                       a.tiles, a.sched, a.out, a.lse, a.n_sched, nb, a.hq, a.hkv, a.scale_log2);
+  const dim3 block(64 * kPrefillWaves);  // either form: four waves of 32 rows, or two of them by two teams
+  auto* kernel = a.d == 128 ? (a.teams ? prefill_teams_kernel<128> : prefill_kernel<128, kPrefillWaves>)
+                            : (a.teams ? prefill_teams_kernel<64> : prefill_kernel<64, kPrefillWaves>);
+  launch_timed_block(a, kernel, grid, block, s, a.k_pool, a.v_pool, a.q, a.items, a.tiles, a.sched, a.out, a.lse,
+                     a.n_sched, nb, a.hq, a.hkv, a.scale_log2);
   return hipGetLastError();
 }
 

@@ -44,6 +44,14 @@ constexpr double kSecondSlotSpeed = 0.80;
 constexpr double kThirdSlotSpeed = 0.65;
 constexpr double kOddXcdSpeed = 0.935;
 
+// A prefill runs half-size workgroups of two teams where the large ones would
+// each have a compute unit to itself and the longest chain has at least this
+// many tiles.  Kernel, large / teams, us, 28 heads (4 KV heads) of 128: 5 tiles
+// 10.7 / 10.5, 7 tiles 11.8 / 11.0, 17 tiles 18.5 / 15.2, 32 tiles 29.9 /
+// 22.4, 40 new tokens after 1,500 (49 tiles) 40.5 / 29.9; past one large
+// workgroup per unit (448 of them, 13 tiles) 18.7 / 25.2.
+constexpr int32_t kPrefillTeamTiles = 8;
+
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 std::atomic<uint64_t> g_plan_uid{0};
@@ -1101,6 +1109,7 @@ int32_t treepo_prefill(treepo_ctx* ctx, int32_t n, const int32_t* nodes, const i
   a.scale_log2 = scale * 1.44269504088896340736f;
   a.out = out;
   a.lse = lse;
+  a.teams = static_cast<int64_t>(a.n_items) * a.hq <= ctx->params.compute_units && pl.items[0].nk >= kPrefillTeamTiles;
   e = timed_launch_attached(ctx, TREEPO_KERNEL_PREFILL, [&](hipEvent_t s0, hipEvent_t s1) {
     a.ev_start = s0;
     a.ev_stop = s1;

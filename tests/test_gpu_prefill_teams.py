@@ -1,0 +1,95 @@
+"""GPU parity of the prefill's two-team form (few workgroups, chains of at least
+8 tiles) at the edges of its 64-row halves, its tile parities and its rule.
+
+Tolerance: the weights carry two bf16 terms (relative error 2^-17), so an
+output moves by at most 2^-17 of the largest |V| it averages (below 5.5 for the
+N(0, 1) rows here: 4.2e-5), and fp32 accumulation adds less than 1e-6.
+"""
+
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from oracle import prefill as PF
+from tests.test_gpu_prefill import _Rig
+
+TOL = 5e-5
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(rig, nodes, lens, step, tag):
+    qb, out, lse = rig.prefill(nodes, lens, step)
+    ref, ref_l = PF.prefill(rig.model, rig.node_kv, nodes, lens, qb, rig.scale)
+    err, err_l = float(np.abs(out - ref).max()), float(np.abs(lse - ref_l).max())
+    print(f"[prefill teams {tag}] max|out-oracle|={err:.3e} max|lse-oracle|={err_l:.3e}", flush=True)
+    assert err <= TOL and err_l <= TOL
+
+
+@pytest.mark.parametrize("d,hq,hkv", [(128, 6, 2), (64, 3, 1)])
+@pytest.mark.parametrize("prefix", [0, 225, 257, 300])
+def test_row_and_tile_edges(prefix, d, hq, hkv):
+    """7, 8 and 9 tiles and more; items of 1, 64, 65 and 128 rows; ragged last tiles."""
+    rig = _Rig(hq, hkv, d, 3 + d + prefix, num_blocks=600)
+    parent = -1
+    if prefix:
+        parent = rig.ctx.new_root(prefix)
+        assert rig.model.new_root(prefix) == parent
+        _check(rig, [parent], [prefix], 0, f"prefix {prefix} d={d}")
+    for i, n in enumerate((1, 31, 63, 64, 65, 127, 128, 129, 193, 224, 225, 256, 257, 289)):
+        x = rig.ctx.new_root(n) if parent < 0 else rig.ctx.fork(parent, 1, n)[0]
+        assert x == (rig.model.new_root(n) if parent < 0 else rig.model.fork(parent, 1, n)[0])
+        _check(rig, [x], [n], 1 + i, f"prefix {prefix} n {n} d={d}")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_rows_that_continue_a_node(d):
+    """New rows that start inside a tile of a node that already holds tokens."""
+    rig = _Rig(4, 2, d, 9, num_blocks=60)
+    x = rig.ctx.new_root(1200)
+    assert rig.model.new_root(1200) == x
+    for i, n in enumerate((270, 17, 1, 95, 130, 64, 31, 200)):
+        _check(rig, [x], [n], i, f"continue {n} d={d}")
+
+
+@pytest.mark.parametrize("items,hq", [(256, 1), (257, 1), (128, 2), (1, 128)])
+def test_rule_edge(items, hq):
+    """256 large workgroups and one more; the most heads of one KV head."""
+    rig = _Rig(hq, 1, 64, 4, num_blocks=2 * items + 20, max_nodes=items + 2)
+    r = rig.ctx.new_root(260)
+    assert rig.model.new_root(260) == r
+    _check(rig, [r], [260], 0, "root")
+    kids = rig.ctx.fork(r, items, 70)
+    assert rig.model.fork(r, items, 70) == kids
+    _check(rig, kids, [1 + i % 70 for i in range(items)], 1, f"items {items} heads {hq}")
+
+
+@pytest.mark.parametrize("sign", [1, -1])
+@pytest.mark.parametrize("at", [5, 37, 137])
+def test_infinite_scores(at, sign):
+    """A key that is infinite in column 0: a NaN row or weight 0 by the sign of
+    the query's column 0, in either team's tiles and for every later row."""
+    import torch
+    n, d = 300, 64
+    rng = np.random.default_rng(3)
+    q, k, v = (torch.tensor(rng.standard_normal((n, 1, d)), dtype=torch.bfloat16) for _ in range(3))
+    q[:, 0, 0] = sign * q[:, 0, 0].abs().clamp(min=0.1)
+    k[at, 0, 0] = float("inf")
+    rig = _Rig(1, 1, d, 1, num_blocks=8)
+    x = rig.ctx.new_root(n)
+    out = torch.empty((n, 1, d), dtype=torch.float32, device="cuda")
+    lse = torch.empty((n, 1), dtype=torch.float32, device="cuda")
+    ws = torch.empty(rig.ctx.prefill_workspace_size([x], [n]), dtype=torch.uint8, device="cuda")
+    print(f"[prefill teams infinite at={at} sign={sign}]", flush=True)
+    rig.ctx.prefill([x], [n], q.cuda(), k.cuda(), v.cuda(), rig.scale, out, lse, ws)
+    torch.cuda.synchronize()
+    s = (q[:, 0].double() @ k[:, 0].double().T) * rig.scale
+    s = s.masked_fill(torch.triu(torch.ones(n, n, dtype=torch.bool), 1), float("-inf"))
+    ref = torch.softmax(s, -1) @ v[:, 0].double()
+    got = out[:, 0].cpu().double()
+    finite = torch.ones(n, dtype=torch.bool)
+    if sign > 0:
+        finite[at:] = False
+        assert torch.isnan(got[at:]).all() and torch.isnan(ref[at:]).all()
+    assert float((got[finite] - ref[finite]).abs().max()) <= TOL
