@@ -491,7 +491,7 @@ int32_t build_plan(const Tree& t, int32_t n_leaves, const int32_t* leaves, PlanM
   for (int32_t x = 0; x < nx; ++x) xcd_mean += xcd_speed(x);
   xcd_mean /= nx;
   const double full_stream = 3 * kMaxStreamTiles / 4;
-  const bool one_round = total_cost <= static_cast<double>(S0) * full_stream;
+  const bool one_round = total_cost <= static_cast<double>(std::max(1, p.guided_wgs)) * full_stream;
   const int64_t planned = one_round ? std::min<int64_t>(total_tiles, S0) : INT64_MAX;
   // One round: stream s closes once the running cost passes quota[s], its
   // share of the total cost in proportion to its slot's and die's speed.  The

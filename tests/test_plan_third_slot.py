@@ -23,3 +23,17 @@ def test_streams_by_cost(d, per_stream, slots):
     cost = _stream_costs(pieces, n_streams)
     assert (cost.sum() >= 24 * 512) == (slots == 768) or d == 128
     assert 0.95 * slots <= n_streams <= slots
+
+
+def test_several_rounds_as_before():
+    """Work past two workgroups' tables (192 cost units each) takes several
+    rounds of short streams at D = 64 too, although three would hold it."""
+    tokens = 32 * 512 * 220 // 4
+    n = 4
+    ops = [("root", tokens), ("append", [0], [tokens]), ("fork", 0, n, 64), ("append", [1, 2, 3, 4], [7] * n)]
+    log = _Log(ops, [1, 2, 3, 4], {0: tokens, **{1 + i: 7 for i in range(n)}})
+    ctx = host_ctx(hq=16, hkv=4, d=64)
+    replay_host(ctx, log)
+    pieces, _, n_streams = _plan_checks(ctx, oracle_model(log), log.leaves, 0)
+    assert 192 * 512 < _stream_costs(pieces, n_streams).sum() < 192 * 768
+    assert n_streams > 768
