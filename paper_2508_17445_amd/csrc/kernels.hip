@@ -1004,8 +1004,11 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(const int2* __restric
 // straight from the pools into registers, the next tile's loads in flight
 // while one is computed (a tile that several leaves share is read by each of
 // them: at these sizes it comes from the caches); the waves' rows then meet
-// in LDS.  Bound by latency: the records, the operands and the merge are
-// three memory round trips.
+// in LDS.  Bound by latency at few tiles -- the records, the operands and the
+// merge are three memory round trips, 4.1 us for one round of 8 waves -- and by
+// the operands' rate into a CU beyond: 1.8 us a round at D = 128 (128 KiB, 30
+// bytes a clock), with each tile's wait leaving the next one's loads in flight;
+// 2.1 us where the compiler drained them (records read per step).
 template <int D, int W>
 __global__ __launch_bounds__(64 * W, 2) void direct_kernel(
     const int4* __restrict__ recs, int32_t stride, const int32_t* __restrict__ node_len,
@@ -1029,54 +1032,60 @@ __global__ __launch_bounds__(64 * W, 2) void direct_kernel(
   // V^T row r16, tokens 8 a .. 8 a + 7
   const int ko0 = tau(0, r16) * D + a * 8, ko1 = tau(1, r16) * D + a * 8;
   const int vo = (a >> 1) * (D * kVGroup) + r16 * kVGroup + (a & 1) * 8;
+  // This wave's records, one per lane (at most kDirectChain / 64 / W = 10), so
+  // that no step waits for its own; the kernel's loads are straight code
+  // between the steps' branches, or the compiler drains them.
+  const int n = stride > wave ? (stride - wave + W - 1) / W : 0;  // steps of this wave
+  const int4 rec = rl[lane < n ? wave + W * lane : 0];
   struct Tile {
     uint4 k[2 * kKS], v[kDB];
-    int valid;
   };
-  auto load = [&](int j, Tile& t) {
-    const int4 r = rl[j];  // wave-uniform
-    t.valid = -1;
-    if (r.x < 0) return;
-    const int64_t off = static_cast<int64_t>(r.x) * kVGroup * D;
+  // (past a shorter chain: the pool's first tile, unused)
+  auto load = [&](int i, Tile& t) {
+    const int hb = __builtin_amdgcn_readlane(rec.x, i);
+    const int64_t off = static_cast<int64_t>(hb < 0 ? 0 : hb) * kVGroup * D;
+    const uint16_t* kt = kh + off;
+    const uint16_t* vt = vh + off;
 #pragma unroll
     for (int ks = 0; ks < kKS; ++ks) {
-      t.k[2 * ks] = *reinterpret_cast<const uint4*>(kh + off + ko0 + ks * 32);
-      t.k[2 * ks + 1] = *reinterpret_cast<const uint4*>(kh + off + ko1 + ks * 32);
+      t.k[2 * ks] = *reinterpret_cast<const uint4*>(kt + ko0 + ks * 32);
+      t.k[2 * ks + 1] = *reinterpret_cast<const uint4*>(kt + ko1 + ks * 32);
     }
 #pragma unroll
-    for (int db = 0; db < kDB; ++db) t.v[db] = *reinterpret_cast<const uint4*>(vh + off + vo + db * 16 * kVGroup);
-    t.valid = r.y;
-    if (r.z >= 0) {
-      const int n = node_len[r.z] - r.w;
-      t.valid = n < 0 ? 0 : (n > kSub ? kSub : n);
-    }
+    for (int db = 0; db < kDB; ++db) t.v[db] = *reinterpret_cast<const uint4*>(vt + vo + db * 16 * kVGroup);
   };
 
-  uint4 qb[kKS];
+  uint4 qb[kKS];  // rows past the group repeat its first; their results are not written
 #pragma unroll
   for (int ks = 0; ks < kKS; ++ks)
-    qb[ks] = r16 < group ? *reinterpret_cast<const uint4*>(q + (row0 + r16) * D + (4 * ks + a) * 8)
-                         : make_uint4(0, 0, 0, 0);
+    qb[ks] = *reinterpret_cast<const uint4*>(q + (row0 + (r16 < group ? r16 : 0)) * D + (4 * ks + a) * 8);
+  int len = 0;
+  if (node_len != nullptr) len = node_len[rec.z < 0 ? 0 : rec.z];
+  Tile t0, t1;
+  if (n > 0) load(0, t0);
+  len -= rec.w;
+  const int count = rec.z < 0 ? rec.y : (len < 0 ? 0 : (len > kSub ? kSub : len));  // of this lane's record
   f32x4 acc[kDB];
 #pragma unroll
   for (int db = 0; db < kDB; ++db) acc[db] = f32x4{0.f, 0.f, 0.f, 0.f};
   float m_ref = -INFINITY, l_sum = 0.f;
 
-  auto compute = [&](const Tile& t) {
-    if (t.valid <= 0) return;
+  auto compute = [&](int i, Tile& t) {
+    const int valid = __builtin_amdgcn_readlane(count, i);
     f32x4 S[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
     for (int ks = 0; ks < kKS; ++ks) {
       S[0] = mfma16(t.k[2 * ks], qb[ks], S[0]);
       S[1] = mfma16(t.k[2 * ks + 1], qb[ks], S[1]);
     }
+    if (valid <= 0) return;
     float s[2][4];
     float mx = -INFINITY;
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        s[b][e] = 8 * a + 4 * b + e < t.valid ? S[b][e] * scale_log2 : -INFINITY;
+        s[b][e] = 8 * a + 4 * b + e < valid ? S[b][e] * scale_log2 : -INFINITY;
         mx = fmaxf(mx, s[b][e]);
       }
     if (__builtin_amdgcn_ballot_w64(mx > m_ref + kLazyMaxSlack) != 0) {
@@ -1092,26 +1101,32 @@ __global__ __launch_bounds__(64 * W, 2) void direct_kernel(
     uint2 p0, pl0, p1, pl1;
     l_sum += softmax_p4(s[0], m_ref, p0, pl0) + softmax_p4(s[1], m_ref, p1, pl1);
     const uint4 P = make_uint4(p0.x, p0.y, p1.x, p1.y), PL = make_uint4(pl0.x, pl0.y, pl1.x, pl1.y);
+    if (valid < kSub) {
 #pragma unroll
-    for (int db = 0; db < kDB; ++db) {
-      uint4 va = t.v[db];
-      if (t.valid < kSub) {
-        const uint2 lo = mask_v4(make_uint2(va.x, va.y), 8 * a, t.valid);
-        const uint2 hi = mask_v4(make_uint2(va.z, va.w), 8 * a + 4, t.valid);
-        va = make_uint4(lo.x, lo.y, hi.x, hi.y);
+      for (int db = 0; db < kDB; ++db) {
+        const uint2 lo = mask_v4(make_uint2(t.v[db].x, t.v[db].y), 8 * a, valid);
+        const uint2 hi = mask_v4(make_uint2(t.v[db].z, t.v[db].w), 8 * a + 4, valid);
+        t.v[db] = make_uint4(lo.x, lo.y, hi.x, hi.y);
       }
-      acc[db] = mfma16(va, PL, mfma16(va, P, acc[db]));
     }
+#pragma unroll
+    for (int db = 0; db < kDB; ++db) acc[db] = mfma16(t.v[db], P, acc[db]);
+#pragma unroll
+    for (int db = 0; db < kDB; ++db) acc[db] = mfma16(t.v[db], PL, acc[db]);
   };
-  Tile t0, t1;
-  int j = wave;
-  if (j < stride) load(j, t0);
-  for (; j < stride; j += 2 * W) {
-    if (j + W < stride) load(j + W, t1);
-    compute(t0);
-    if (j + W >= stride) break;
-    if (j + 2 * W < stride) load(j + 2 * W, t0);
-    compute(t1);
+  int i = 0;
+  for (; i + 2 < n; i += 2) {
+    load(i + 1, t1);
+    compute(i, t0);
+    load(i + 2, t0);
+    compute(i + 1, t1);
+  }
+  if (i + 1 < n) {
+    load(i + 1, t1);
+    compute(i, t0);
+    compute(i + 1, t1);
+  } else if (i < n) {
+    compute(i, t0);
   }
 
   // ---- the waves' rows: m* = max m, L = sum l 2^(m - m*), out = sum 2^(m - m*) O / L

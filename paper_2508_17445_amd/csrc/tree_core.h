@@ -113,19 +113,19 @@ enum PlanMode : int32_t { kModeTree = 0, kModeNaive = 1 };
 constexpr int64_t kStridedCombineBytes = int64_t{8} << 20;
 
 // Rule of the direct form (Plan::direct): its time is a floor of 4 us plus, per
-// round of 8 tiles of the longest chain, 1.05 us at D = 64 and 2.1 at 128
-// (more once the keys pass two per CU); the streams and their combine need two
+// round of 8 tiles of the longest chain, 0.9 us at D = 64 and 1.8 at 128 (more
+// once the keys pass two per CU); the streams and their combine need two
 // launches, 10 us at the least, and grow with the KV bytes.  Measured, kernels
 // and the gap between them, streams / direct, D = 128 and 4 KV heads, three
 // quarters of every chain shared:
 //   keys   tiles: 5        20         40         64
-//     16   13.0 /  5.7  11.9 / 10.4 13.3 / 16.0 14.5 / 21.1
-//     64   14.5 /  5.6  15.4 / 10.6 18.2 / 16.3 20.4 / 21.8
-//    256   15.2 /  6.4  21.2 / 10.8 25.3 / 18.6 27.0 / 26.2
-//    512   20.3 / 10.1  25.1 / 20.0 31.3 / 33.9
-//   1024   22.6 / 16.9  32.1 / 37.9                          (8 KV heads)
-// and D = 64: 16 keys 40 tiles 10.7 / 9.5, 64 keys 64 tiles 15.2 / 12.9, 256
-// keys 64 tiles 21.8 / 15.1.  So the bounds, as tiles times D:
+//     16   13.0 /  6.0  11.8 /  9.4 13.4 / 13.8 14.7 / 20.3
+//     64   14.5 /  5.9  16.4 /  9.5 17.6 / 14.1 20.1 / 20.4
+//    256   15.8 /  6.2  20.4 / 10.0 23.8 / 15.6 25.9 / 23.7
+//    512   20.6 / 10.5  24.9 / 17.7 30.3 / 30.5
+//   1024   22.5 / 17.1  31.1 / 34.3                          (8 KV heads)
+// and D = 64: 16 keys 40 tiles 10.9 / 8.9, 64 keys 64 tiles 15.2 / 11.9, 256
+// keys 64 tiles 21.5 / 12.4.  So the bounds, as tiles times D:
 constexpr int32_t kDirectMaxRows = 16;           // query rows of a key: one 16-row block
 constexpr int64_t kDirectMaxKeys = 1024;         // (leaf, KV head) pairs
 constexpr int64_t kDirectFewKeys = 64;           // below: the streams' workgroups are few and short too
