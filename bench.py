@@ -747,7 +747,7 @@ python3 bench.py --summarize prefill --config {cfg_id} --dir gpurun_out/pfprof/c
 ```
 
 Each step is one `treepo_prefill` call over all {len(plens)} prompts (fresh root nodes
-every step): one KV-append launch (pieces read from the uploaded tables), then one prefill launch.
+every step): one KV-append launch (which also moves the tables from pinned memory), then one prefill launch.
 Prefill dispatches in order: {warm} warm-up, {steps} timed, 1 with events attached (then the
 per-rollout baseline's).
 
@@ -761,8 +761,8 @@ and query head): {flops} -> {flops / (avg * 1e-6) / 1e12:.1f} TFLOP/s on the
 trace average = {flops / (avg * 1e-6) / 1e12 / 2500:.3f} of the 2.5 PFLOP/s
 bf16 dense peak.  The same run's bench line: the kernel at
 {b["kernel_avg_ms"] * 1e3:.1f} us with events attached to it
-({b["roofline"]["achieved"]} TFLOP/s), the whole call (append + host tables
-+ upload + prefill) at {b["ms_per_step"] * 1e3:.1f} us""" + (f""", and prefilling every
+({b["roofline"]["achieved"]} TFLOP/s), the whole call (host tables + append
++ prefill) at {b["ms_per_step"] * 1e3:.1f} us""" + (f""", and prefilling every
 prompt once per rollout ({naive["prompt_copies"]} copies) at {naive["ms_per_step"] * 1e3:.0f} us
 ({naive["speedup_shared_vs_per_rollout"]}x).""" if naive else ".") + f"""
 
@@ -821,10 +821,10 @@ library's events attached to the kernel):
 | advantage_kernel | {s0["Calls"]} | {float(s0["AverageNs"]) / 1e3:.2f} | {float(s0["MinNs"]) / 1e3:.2f} | {float(s0["MaxNs"]) / 1e3:.2f} |
 
 The bench line of the same run: {b["call_ms"] * 1e3:.1f} us per call back to back (host index
-arrays cached for the tree shape and leaf list, their upload through pinned
-staging, the kernel), {b.get("kernel_avg_ms", float("nan")) * 1e3:.1f} us on the kernel's attached events,
-{b["value"] / 1e6:.1f} M trajectories/s.  One workgroup; the time is dependent global
-loads (sub-group members, each pair's sub-group mean), not bandwidth.
+arrays cached for the tree shape and leaf list, their copy to pinned memory,
+the kernel), {b.get("kernel_avg_ms", float("nan")) * 1e3:.1f} us on the kernel's attached events,
+{b["value"] / 1e6:.1f} M trajectories/s.  One workgroup; the time is latency (the
+index image read once over PCIe into LDS, the sums, the parents' means in LDS).
 
 advantage.hip sha256: {hashlib.sha256(open(os.path.join(ROOT, "paper_2508_17445_amd", "csrc", "advantage.hip"), "rb").read()).hexdigest()}
 """
@@ -906,7 +906,7 @@ def _decode_line(args):
                      "frac": round(achieved_kern / PEAK_HBM_GBPS, 4), "traffic": _measured_traffic(cfg_id),
                      "kernel": "partial_kernel<128>", "kernel_avg_ms": round(kern_ms, 5),
                      "launches_per_step": launches, "algorithmic_bytes_per_launch": round(nbytes)},
-        "combine_avg_ms": round(comb_ms, 5),
+        "combine_avg_ms": None if comb_ms is None else round(comb_ms, 5),  # small plans have no combine
     }
     if w.fused:
         line["config"]["leaf_chain_tokens_timed"] = [w.chain0 + tm["first"], w.chain0 + tm["first"] + args.steps - 1]

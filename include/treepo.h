@@ -232,7 +232,9 @@ int32_t treepo_decode_workspace_size(treepo_ctx* ctx, int32_t n_leaves,
  *   workspace  device, 256-byte aligned, >= treepo_decode_workspace_size(..., TREEPO_MODE_TREE)
  * Cascade schedule: every node's K/V is read once and scored against all of
  * its descendant leaves' query rows (the nested sub-groups G_j of Sec. 2.3);
- * per-node partials are merged with a log-sum-exp combine (partial rows in
+ * per-node partials are merged with a log-sum-exp combine (small decodes run
+ * one workgroup per leaf and KV head over the whole chain instead, in one
+ * kernel with fp32 results; partial rows in
  * fp32, or, for schedules whose partials far exceed the L2, in block floating
  * point -- 14-bit mantissas under a shared exponent per 4 values: an output
  * then moves by less than 2^-13 of the largest |V| value it averages;
@@ -416,7 +418,7 @@ int32_t treepo_export_blocks(treepo_ctx* ctx, int32_t n_leaves, const int32_t* l
 
 /* Kernel kinds for treepo_profile_read. */
 #define TREEPO_KERNEL_APPEND 0  /* KV scatter into the pools                      */
-#define TREEPO_KERNEL_PARTIAL 1 /* node partials, one workgroup per stream         */
+#define TREEPO_KERNEL_PARTIAL 1 /* node partials, or the whole decode of a small plan */
 #define TREEPO_KERNEL_COMBINE 2 /* log-sum-exp merge of each leaf's partials      */
 #define TREEPO_KERNEL_ADVANTAGE 3 /* TreePO advantage over the leaves' sub-groups  */
 #define TREEPO_KERNEL_PREFILL 4 /* causal attention of prefilled tokens          */
