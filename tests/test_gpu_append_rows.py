@@ -54,9 +54,9 @@ def test_append_rows(counts, d, hkv, bt):
     assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
 
 
-@pytest.mark.parametrize("n", [1, 128, 129, 300])
+@pytest.mark.parametrize("n", [1, 32, 33, 128, 256, 257, 300])
 def test_one_token_steps(n):
-    """One token per leaf at every place of a 16-row group; several launches past 128 leaves."""
+    """One token per leaf at every place of a 16-row group; both batch sizes, several launches past 256 leaves."""
     print(f"[append steps n={n}]", flush=True)
     rng = np.random.default_rng(2)
     rig = _Rig(2, 2, 64, 1, num_blocks=n + 1, live=True)
