@@ -504,7 +504,7 @@ def _summarize_trace(cfg_id, d):
     per_mode = warm + 2 * steps + max(steps, DIST_MIN_STEPS)   # the launches of _time_mode per mode
     modes = 2 if "naive_baseline" in b else 1
     lines, avg = [], {}
-    names = ("partial_kernel", "combine_kernel") + (("kv_append_kernel",) if "append_avg_ms" in b else ())
+    names = ("partial_kernel", "combine_kernel") + (("kv_step_kernel",) if "append_avg_ms" in b else ())
     for kname in names:
         ks = [r for r in rows if kname in r["Kernel_Name"]]
         if not ks:
