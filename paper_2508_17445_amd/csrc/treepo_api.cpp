@@ -408,6 +408,18 @@ int32_t get_plan(treepo_ctx* ctx, int32_t n, const int32_t* leaves, int32_t mode
   int32_t st = treepo::build_plan(ctx->tree, n, leaves, static_cast<PlanMode>(mode), ctx->params,
                                   &cp.plan, &err);
   if (st != treepo::kOk) return fail(ctx, st, err);
+  // The third workgroup's streams add partial entries; a plan that the no-alloc
+  // scratch holds with two keeps two.
+  const int64_t n_streams = static_cast<int64_t>(cp.plan.streams.size());
+  if (n_streams > ctx->params.guided_wgs && n_streams <= ctx->params.concurrent_wgs &&
+      static_cast<size_t>(cp.plan.partial_rows) * (static_cast<size_t>(ctx->cfg.head_dim) + 2) * sizeof(float) +
+              (cp.plan.blocks.size() + 2 * cp.plan.comb_count.size()) * sizeof(int32_t) + 4 * kAlign >
+          treepo::kNoAllocScratchBytes) {
+    PlanParams two = ctx->params;
+    two.concurrent_wgs = two.guided_wgs;
+    st = treepo::build_plan(ctx->tree, n, leaves, static_cast<PlanMode>(mode), two, &cp.plan, &err);
+    if (st != treepo::kOk) return fail(ctx, st, err);
+  }
   treepo::direct_table(ctx->tree, n, leaves, ctx->params, &cp.plan);
   const Plan& p = cp.plan;
   size_t off = 0;

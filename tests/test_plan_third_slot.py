@@ -37,3 +37,20 @@ def test_several_rounds_as_before():
     pieces, _, n_streams = _plan_checks(ctx, oracle_model(log), log.leaves, 0)
     assert 192 * 512 < _stream_costs(pieces, n_streams).sum() < 192 * 768
     assert n_streams > 768
+
+
+@pytest.mark.parametrize("n,slots", [(4, 768), (50, 512)])
+def test_scratch_limit_keeps_two(n, slots):
+    """One very long leaf cut over every stream sets the slot stride of all
+    keys: where three workgroups' entries would pass the 64 MiB of the no-alloc
+    scratch, the plan keeps two."""
+    big = 32 * 512 * 30
+    ctx = host_ctx(hq=8, hkv=1, d=64)
+    r = ctx.new_root(64)
+    ctx.kv_commit([r], [64])
+    long_leaf, = ctx.fork(r, 1, big)
+    kids = [long_leaf] + ctx.fork(r, n - 1, 64)
+    ctx.kv_commit(kids, [big] + [5] * (n - 1))
+    _, _, _, n_streams = ctx.export_plan(kids)
+    assert 0.95 * slots <= n_streams <= slots
+    assert ctx.workspace_size(kids) < 64 << 20
